@@ -290,11 +290,57 @@ __global__ __launch_bounds__(kFinCh * G) void bn_bwd_finalize_kernel(const float
   }
 }
 
+// The finalize inside the apply, for few partials: every block adds all of them by itself, so
+// a launch of its own (3.9 us for the emptiest kernel, as much as a small apply) goes away.
+// kFoldMax bounds nblocks * c: 16 partials a thread and 32 KiB a block, which the apply
+// blocks read from L2.  Finalize + apply -> apply: 2048 rows of 32 channels 8.2 -> 4.9 us, 2450
+// of 128 8.5 -> 6.9; with twice the partials the two launches are as fast.
+constexpr int kFoldMax = 4096;
+
+// this block's folded constants coef[4][c] in LDS from the reduce's partials (fp64 sums in a
+// fixed order: G thread groups per channel, each over nblocks / G partials G apart, then the
+// groups in order); block 0 publishes dgamma and dbeta.  Without partials (nblocks 0) the
+// constants come from the given dgamma and dbeta.
+__device__ __forceinline__ void fold_partials(const float2* part, int nblocks, const BnArgs& a, const float* save_mean,
+                                              const float* save_rstd, const float* gamma, const float* beta,
+                                              float* dgamma, float* dbeta, double (*s_sum)[2], float* s_coef) {
+  const int c = a.c, t = threadIdx.x;
+  const int G = c < kThreads ? kThreads / c : 1;
+  for (int c0 = 0; c0 < c; c0 += kThreads) {  // (one trip unless c > kThreads, where G is 1)
+    const int ch = c0 + (G > 1 ? t % c : t), g = G > 1 ? t / c : 0;
+    double p = 0, q = 0;
+    if (ch < c && g < G) {
+#pragma unroll 16
+      for (int b = g; b < nblocks; b += G) {
+        const float2 v = part[(int64_t)b * c + ch];
+        p += v.x;
+        q += v.y;
+      }
+      s_sum[t][0] = p;
+      s_sum[t][1] = q;
+    }
+    __syncthreads();
+    if (ch < c && g == 0) {
+      for (int k = 1; k < G; ++k) {
+        p += s_sum[k * c + ch][0];
+        q += s_sum[k * c + ch][1];
+      }
+      const float db = nblocks > 0 ? (float)p : dbeta[ch], dg = nblocks > 0 ? (float)q : dgamma[ch];
+      bn_bwd_fold(gamma[ch], beta[ch], save_mean[ch], save_rstd[ch], dg, db, a.m, s_coef[ch], s_coef[c + ch],
+                  s_coef[2 * c + ch], s_coef[3 * c + ch]);
+      if (blockIdx.x == 0 && nblocks > 0) {
+        dbeta[ch] = db;
+        dgamma[ch] = dg;
+      }
+    }
+    __syncthreads();
+  }
+}
+
 // --- backward apply: dy = gamma * rstd * (dz - dbeta/m - xhat * dgamma/m); residual_grad += g
-// (row layout, the finalize's folded constants in registers, four rows in flight)
-__global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(BnArgs a, const bf16_t* g, const bf16_t* y,
-                                                                const float* coef, bf16_t* dy, bf16_t* res_grad,
-                                                                int64_t rows_per_block) {
+// (row layout, the folded constants in registers, four rows in flight)
+__device__ __forceinline__ void bwd_apply_rows(const BnArgs& a, const bf16_t* g, const bf16_t* y, const float* coef,
+                                               bf16_t* dy, bf16_t* res_grad, int64_t rows_per_block) {
   const int c = a.c;
   const RowLayout L = row_layout(c);
   const int t = threadIdx.x;
@@ -341,6 +387,26 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(BnArgs a, const 
       }
     }
   }
+}
+
+// the constants from the finalize kernel
+__global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(BnArgs a, const bf16_t* g, const bf16_t* y,
+                                                                const float* coef, bf16_t* dy, bf16_t* res_grad,
+                                                                int64_t rows_per_block) {
+  bwd_apply_rows(a, g, y, coef, dy, res_grad, rows_per_block);
+}
+
+// the constants from the reduce's partials, or from given dgamma and dbeta (fold_partials)
+__global__ __launch_bounds__(kThreads) void bn_bwd_fold_apply_kernel(BnArgs a, const bf16_t* g, const bf16_t* y,
+                                                                     const float2* part, int nblocks,
+                                                                     const float* save_mean, const float* save_rstd,
+                                                                     const float* gamma, const float* beta,
+                                                                     float* dgamma, float* dbeta, bf16_t* dy,
+                                                                     bf16_t* res_grad, int64_t rows_per_block) {
+  extern __shared__ float s_coef[];  // [4][c]
+  __shared__ double s_sum[kThreads][2];
+  fold_partials(part, nblocks, a, save_mean, save_rstd, gamma, beta, dgamma, dbeta, s_sum, s_coef);
+  bwd_apply_rows(a, g, y, s_coef, dy, res_grad, rows_per_block);
 }
 
 size_t reduce_smem(int c) {
@@ -432,6 +498,15 @@ hipError_t bn_bwd_launch(const BnArgs& a, const bf16_t* g, const bf16_t* y, cons
   trace_end(KC_BN_BWD_REDUCE);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (dy != nullptr && (int64_t)nb * a.c <= kFoldMax) {
+    int64_t rows = 0;
+    const int ab = apply_blocks(a.m, a.c, &rows);
+    trace_begin(KC_BN_BWD_APPLY);
+    NUMBAT_LAUNCH(bn_bwd_fold_apply_kernel, dim3(ab), dim3(kThreads), 4 * a.c * sizeof(float), s, a, g, y,
+                  (const float2*)part, nb, save_mean, save_rstd, gamma, beta, dgamma, dbeta, dy, res_grad, rows);
+    trace_end(KC_BN_BWD_APPLY);
+    return hipGetLastError();
+  }
   trace_begin(KC_BN_BWD_FINALIZE);
   // about eight partial rows per lane
   const dim3 fgrid((a.c + kFinCh - 1) / kFinCh);
@@ -456,6 +531,20 @@ hipError_t bn_bwd_launch(const BnArgs& a, const bf16_t* g, const bf16_t* y, cons
   trace_begin(KC_BN_BWD_APPLY);
   NUMBAT_LAUNCH(bn_bwd_apply_kernel, dim3(anb), dim3(kThreads), 0, s, a, g, y, (const float*)coef, dy, res_grad,
                 arpb);
+  trace_end(KC_BN_BWD_APPLY);
+  return hipGetLastError();
+}
+
+hipError_t bn_bwd_dy_launch(const BnArgs& a, const bf16_t* g, const bf16_t* y, const float* save_mean,
+                            const float* save_rstd, const float* gamma, const float* beta, bf16_t* dy,
+                            const float* dgamma, const float* dbeta, hipStream_t s) {
+  int64_t rows = 0;
+  const int nb = apply_blocks(a.m, a.c, &rows);
+  trace_begin(KC_BN_BWD_APPLY);
+  // (with no partials the kernel only reads dgamma and dbeta)
+  NUMBAT_LAUNCH(bn_bwd_fold_apply_kernel, dim3(nb), dim3(kThreads), 4 * a.c * sizeof(float), s, a, g, y,
+                (const float2*)nullptr, 0, save_mean, save_rstd, gamma, beta, const_cast<float*>(dgamma),
+                const_cast<float*>(dbeta), dy, (bf16_t*)nullptr, rows);
   trace_end(KC_BN_BWD_APPLY);
   return hipGetLastError();
 }

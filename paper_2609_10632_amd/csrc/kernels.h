@@ -253,6 +253,11 @@ hipError_t bn_bwd_launch(const BnArgs& a, const bf16_t* g, const bf16_t* y, cons
                          const float* save_rstd, const float* gamma, const float* beta, bf16_t* dy, float* dgamma,
                          float* dbeta, bf16_t* res_grad, float* part2, int nblocks, float* coef, hipStream_t s);
 
+// dy alone, from dgamma and dbeta as bn_bwd_launch formed them (no reduce, no finalize)
+hipError_t bn_bwd_dy_launch(const BnArgs& a, const bf16_t* g, const bf16_t* y, const float* save_mean,
+                            const float* save_rstd, const float* gamma, const float* beta, bf16_t* dy,
+                            const float* dgamma, const float* dbeta, hipStream_t s);
+
 // SPPF max pool (5x5, stride 1, padding 2) and nearest 2x upsampling (pool.hip): n, h, w
 // of the pooled / low-resolution tensor, c channels (a multiple of 8), pixel strides of x
 // (and dx) and y (and dy); idx: one byte per element of y, dense [n][h][w][c]

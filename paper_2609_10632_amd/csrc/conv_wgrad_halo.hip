@@ -137,9 +137,9 @@ __global__ __launch_bounds__(512) void wgrad_halo_kernel(WgradArgs a, WhGeom g) 
 
   // This lane's part of load slot u of its wave (instruction n = wave + 8 u of a stage):
   // the byte offset of its 16 bytes from the step's base (kOobH: zeros) and the position of
-  // its pixel: for a halo pixel (row + 1) | (column + 1) << 16 relative to the patch origin
-  // (the dy pixels of a patch are always inside); in the 1x1 form the pixel's index within
-  // the step (the last step may pass the last pixel).
+  // its pixel: (row + 1) | (column + 1) << 16 relative to the patch origin (a patch may pass
+  // the image's last row or column: dy and input pixels there read zeros); in the 1x1 form
+  // the pixel's index within the step (the last step may pass the last pixel).
   uint32_t loff[LW];
   uint32_t lpos[LW];
 #pragma unroll
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(512) void wgrad_halo_kernel(WgradArgs a, WhGeom g) 
       const int ch = RB == 128 ? (slot ^ (4 * ((pr >> 1) & 1))) : slot;  // 16-byte chunk (8 channels)
       const int o = o0 + 8 * ch;
       if (o < a.co) loff[u] = (uint32_t)(((pr / PC) * a.w + pr % PC) * (uint32_t)a.dy_pix * 2u + (uint32_t)o * 2u);
-      if constexpr (KH == 1) lpos[u] = (uint32_t)pr;
+      lpos[u] = KH == 3 ? (uint32_t)(pr / PC + 1) | ((uint32_t)(pr % PC + 1) << 16) : (uint32_t)pr;
     } else if (n < NDY + NHA) {
       const int hb = bl - NDY * 1024;
       const int hp = hb / HRB, ch = (hb % HRB) / 16;
@@ -418,61 +418,69 @@ int wh_ob(int co) {
   return pad3 <= pad2 ? 3 : 2;
 }
 
+// Whether a configuration that pads channels or pixels (`pixels` staged in all) is still the
+// one to run: it executes at most kPadMost times the products of the general kernel, whose
+// tiles pad kh kw c_in to 128 columns.  Per product this kernel is 15-35% faster (8 x 52 x 52,
+// 192 -> 80 on 20 x 4 patches, 15% of them outside the image: 27.3 -> 22.3 us; 12 x 13 x 13 x
+// 256 18.1 -> 14.7; 16 x 33 x 33 x 80 18.1 -> 12.7).
+constexpr double kPadMost = 1.15;
+bool wh_cheaper(const WgradArgs& a, const WhCfg& c, int64_t pixels) {
+  auto up = [](int64_t v, int64_t q) { return (v + q - 1) / q * q; };
+  const double here = (double)pixels * up(a.co, 32 * c.ob) * up(a.ci, c.ck) * c.kh * c.kh;
+  int64_t rows = up(a.co, 64);
+  for (const int b : {96, 128})
+    if (up(a.co, b) < rows) rows = up(a.co, b);
+  return here <= kPadMost * (double)a.m * rows * up(a.ktot, 128);
+}
+
 // The configuration for a problem, or ob = 0 where the kernel does not apply.
 WhCfg wgrad_halo_cfg(const WgradArgs& a) {
   WhCfg c{0, 0, 0, 0, 0};
   if (a.ho != a.h || a.wo != a.w || a.sh != 1 || a.sw != 1) return c;
-  if (a.co % 8 != 0 || a.x_pix % 8 != 0 || a.dy_pix % 8 != 0 || a.ci < 32) return c;
+  if (a.co % 8 != 0 || a.ci % 8 != 0 || a.x_pix % 8 != 0 || a.dy_pix % 8 != 0) return c;
 #ifdef NUMBAT_TUNING
   if (const char* e = getenv("NUMBAT_WH_OFF")) {
     if (atoi(e)) return c;
   }
 #endif
   if (a.kh == 1 && a.kw == 1 && a.ph == 0 && a.pw == 0) {
-    // 1x1: steps of 64 consecutive pixels; the largest chunk of 288, 192, 144 or 96 input
-    // channels that divides c_in
-    int ck = 0;
-    for (const int k : {288, 192, 144, 96})
-      if (ck == 0 && a.ci % k == 0) ck = k;
-    if (ck == 0 || a.m >= (1ll << 36)) return c;
-#ifdef NUMBAT_TUNING
-    if (const char* e = getenv("NUMBAT_WH1_OFF")) {
-      if (atoi(e)) return c;
+    // 1x1: steps of 64 consecutive pixels; of the chunks of 288, 192, 144 and 96 input
+    // channels the one that pads c_in least, the largest on a tie
+    int ck = 0, pad = 0;
+    for (const int k : {288, 192, 144, 96}) {
+      const int p = (a.ci + k - 1) / k * k;
+      if (ck == 0 || p < pad) ck = k, pad = p;
     }
-    if (const char* e = getenv("NUMBAT_WH1_MAXCI")) {
-      if (a.ci > atoi(e)) return c;
-    }
-#endif
+    if (a.m >= (1ll << 36)) return c;
     c.ob = wh_ob(a.co);
     c.ck = ck;
     c.pr = 1;
     c.pc = 64;
     c.kh = 1;
-    return c;
+    return pad == a.ci || wh_cheaper(a, c, (int64_t)a.m) ? c : WhCfg{0, 0, 0, 0, 0};
   }
   if (a.kh != 3 || a.kw != 3 || a.ph != 1 || a.pw != 1) return c;
-  int ck = 0;
-  if (a.ci % 32 == 0) ck = 32;
-  else if (a.ci % 48 == 0) ck = 48;
-  else return c;
-  int pr = 0, pc = 0;
-  if (a.h % 8 == 0 && a.w % 16 == 0) pr = 8, pc = 16;
-  else if (a.h % 20 == 0 && a.w % 8 == 0) pr = 20, pc = 8;
-  else if (a.h % 20 == 0 && a.w % 4 == 0) pr = 20, pc = 4;
-  else return c;
   // offsets within one image (plus its halo) are 32-bit
   const int64_t pix = a.x_pix > a.dy_pix ? a.x_pix : a.dy_pix;
   if (((int64_t)a.h * a.w + 2 * (int64_t)a.w + 2) * pix * 2 >= (1ll << 31) - (1ll << 24)) return c;
-  c.ob = ck == 32 ? wh_ob(a.co) : 2;
-  c.ck = ck;
-  c.pr = pr;
-  c.pc = pc;
+  // the chunk that pads c_in least (32 on a tie), the patch that pads the image least (the
+  // first on a tie)
+  const int pad32 = (a.ci + 31) / 32 * 32, pad48 = (a.ci + 47) / 48 * 48;
+  c.ck = pad48 < pad32 ? 48 : 32;
+  c.ob = c.ck == 32 ? wh_ob(a.co) : 2;
   c.kh = 3;
-  return c;
+  int64_t area = 0;
+  constexpr int kPatch[3][2] = {{8, 16}, {20, 8}, {20, 4}};
+  for (const auto& p : kPatch) {
+    const int64_t ar = (int64_t)((a.h + p[0] - 1) / p[0]) * p[0] * ((a.w + p[1] - 1) / p[1]) * p[1];
+    if (area == 0 || ar < area) area = ar, c.pr = p[0], c.pc = p[1];
+  }
+  const bool whole = area == (int64_t)a.h * a.w && (pad32 == a.ci || pad48 == a.ci);
+  return whole || wh_cheaper(a, c, area * a.n) ? c : WhCfg{0, 0, 0, 0, 0};
 }
 
 int64_t wh_npatch(const WgradArgs& a, const WhCfg& c) {
-  return c.kh == 1 ? (a.m + 63) / 64 : (int64_t)a.n * (a.h / c.pr) * (a.w / c.pc);
+  return c.kh == 1 ? (a.m + 63) / 64 : (int64_t)a.n * ((a.h + c.pr - 1) / c.pr) * ((a.w + c.pc - 1) / c.pc);
 }
 
 template <int OB, int CK, int PR, int PC, int S, int KH>
@@ -540,8 +548,8 @@ hipError_t wgrad_halo_launch(const WgradArgs& args, hipStream_t s) {
   if (c.ob == 0 || a.ktot != c.kh * c.kh * a.ci || a.rows_per_split < 1) return hipErrorInvalidValue;
   a.remap = 1;
   WhGeom g;
-  g.pcols = c.kh == 3 ? a.w / c.pc : 1;
-  g.ppi = c.kh == 3 ? (a.h / c.pr) * g.pcols : 1;
+  g.pcols = c.kh == 3 ? (a.w + c.pc - 1) / c.pc : 1;
+  g.ppi = c.kh == 3 ? ((a.h + c.pr - 1) / c.pr) * g.pcols : 1;
   g.npatch = (int32_t)wh_npatch(a, c);
   g.pps = (int32_t)a.rows_per_split;
   g.dppi = make_fastdiv((uint32_t)g.ppi);

@@ -178,7 +178,7 @@ bool narrow(const ConvDesc& d) { return d.ci % 8 != 0; }
 size_t x8_bytes(const ConvDesc& d) { return round_up((size_t)d.n * d.h * d.w * 16, 256); }
 
 // 3x3, stride-1, padding-1 problems whose reduction channels (c_in for the forward, c_out
-// for the data gradient) are 16-multiples of at least 32 run the halo kernel: it stages each
+// for the data gradient) are 8-multiples run the halo kernel: it stages each
 // tile's input halo once per 32-channel chunk instead of gathering every tap
 bool halo_geometry(const ConvDesc& d) {
   bool on = d.kh == 3 && d.kw == 3 && d.sh == 1 && d.sw == 1 && d.ph == 1 && d.pw == 1;
@@ -188,16 +188,51 @@ bool halo_geometry(const ConvDesc& d) {
   return on;
 }
 TileCfg halo_tile(const ConvDesc& d, int cs, int nout, bool bt) {
-  if (!halo_geometry(d) || cs % 16 != 0 || cs < 32 || (int64_t)nout * 9 * cs * 2 >= ((int64_t)1 << 31) - 16)
+  const int64_t pix2 = (bt ? d.y_pix : d.x_pix) * 2;
+  // (a tile's halo, of at most 256 + 2 w + 2 or 10 w + 34 pixels, within 31-bit byte offsets)
+  if (!halo_geometry(d) || cs % 8 != 0 || (int64_t)nout * 9 * cs * 2 >= ((int64_t)1 << 31) - 16 ||
+      (10ll * d.w + 258) * pix2 >= (1ll << 31) - (1ll << 25))
     return TileCfg{0, 0, -1, kVariantGeneric};
-  return convhalo_pick(d.m, nout, d.h, d.w, bt);
+  return convhalo_pick(d.m, nout, cs, d.h, d.w, bt);
 }
+
+// The reduction-splitting kernel's tile, where it is the one to run; its gathers address the
+// whole tensor with 31-bit byte offsets.
+TileCfg split_tile(const ConvDesc& d, bool dgrad) {
+  const TileCfg none{0, 0, -1, kVariantGeneric};
+  if (narrow(d)) return none;
+  constexpr int64_t kSpan = (1ll << 31) - (1ll << 25);
+  if ((int64_t)d.co * d.kh * d.kw * d.ci * 2 >= kSpan) return none;
+  if (!dgrad) {
+    if (((int64_t)d.n * d.h * d.w + 8ll * d.w) * d.x_pix * 2 >= kSpan) return none;
+    return convsplit_pick(d.m, d.co, d.ci, d.kh * d.kw * d.ci, 1, false);
+  }
+  if (((int64_t)d.n * d.ho * d.wo + 8ll * d.wo) * d.y_pix * 2 >= kSpan) return none;
+  const int64_t mp = (int64_t)d.n * ((d.h + d.sh - 1) / d.sh) * ((d.w + d.sw - 1) / d.sw);
+  const int tp = ((d.kh + d.sh - 1) / d.sh) * ((d.kw + d.sw - 1) / d.sw);
+  return convsplit_pick(mp, d.ci, d.co, tp * d.co, d.sh * d.sw, true);
+}
+
+size_t stats_bytes(const ConvDesc& d, int bm) {
+  return round_up((size_t)((d.m + bm - 1) / bm) * d.co * sizeof(float2), 256);
+}
+
+// bytes of the static scratch of numbat_conv_fwd_noalloc
+constexpr size_t kScratchBytes = (size_t)8 << 20;
 
 TileCfg fwd_tile(const ConvDesc& d) {
   if (narrow(d)) return narrow_pick(d.co);
-  const TileCfg h = halo_tile(d, d.ci, d.co, false);
-  if (h.variant == kVariantHalo) return h;
-  return convgemm_pick(d.m, d.co, d.ci, d.kh * d.kw * d.ci, 1, false);
+  const TileCfg sp = split_tile(d, false);
+  if (sp.variant == kVariantSplit) return sp;
+  TileCfg t = halo_tile(d, d.ci, d.co, false);
+  const int ktot = d.kh * d.kw * d.ci;
+  if (t.variant != kVariantHalo) t = convgemm_pick(d.m, d.co, d.ci, ktot, 1, false);
+  // Channel counts that also run on the register-staged kernel (not a multiple of 16, or below
+  // 32) take its 256-row tiles where only those keep the statistics partials within
+  // numbat_conv_fwd_noalloc's scratch.
+  if ((d.ci % 16 != 0 || d.ci < 32) && with_header(stats_bytes(d, t.bm)) > kScratchBytes)
+    return convgemm_pick(d.m, d.co, d.ci, ktot, 1, false, true);
+  return t;
 }
 
 // the prologue-fused forward's tile: the halo kernel on any grid (kVariantGeneric when
@@ -206,13 +241,13 @@ TileCfg prologue_tile(const ConvDesc& d) {
   if (!halo_geometry(d) || narrow(d) || d.ci % 16 != 0 || d.ci < 32 || d.ci > kProMaxC ||
       (int64_t)d.co * 9 * d.ci * 2 >= ((int64_t)1 << 31) - 16)
     return TileCfg{0, 0, -1, kVariantGeneric};
-  return convhalo_pick(d.m, d.co, d.h, d.w, false, true);
+  return convhalo_pick(d.m, d.co, d.ci, d.h, d.w, false, true);
 }
 
 // the data gradient with the BN + SiLU backward prologue: the halo kernel's tile for the
 // problem (kVariantGeneric when the kernel does not take it)
 TileCfg bwd_prologue_tile(const ConvDesc& d) {
-  if (d.co > kProMaxC || narrow(d)) return TileCfg{0, 0, -1, kVariantGeneric};
+  if (d.co > kProMaxC || d.co % 16 != 0 || d.co < 32 || narrow(d)) return TileCfg{0, 0, -1, kVariantGeneric};
   return halo_tile(d, d.co, d.ci, true);
 }
 
@@ -220,12 +255,7 @@ TileCfg bwd_prologue_tile(const ConvDesc& d) {
 // forward's (one workspace serves both)
 size_t fwd_stats_bytes(const ConvDesc& d) {
   const TileCfg t = fwd_tile(d), tp = prologue_tile(d);
-  int64_t mt = (d.m + t.bm - 1) / t.bm;
-  if (tp.variant == kVariantHalo) {
-    const int64_t mp = (d.m + tp.bm - 1) / tp.bm;
-    mt = mp > mt ? mp : mt;
-  }
-  return round_up((size_t)mt * d.co * sizeof(float2), 256);
+  return stats_bytes(d, tp.variant == kVariantHalo && tp.bm < t.bm ? tp.bm : t.bm);
 }
 
 size_t fwd_ws(const ConvDesc& d) { return fwd_stats_bytes(d); }
@@ -465,7 +495,6 @@ numbat_status conv_fwd_launch(const ConvDesc& d, const void* x, const void* w, v
 // Static scratch for numbat_conv_fwd_noalloc: a file-scope device array (each GPU holds its
 // own copy for the life of the process).  Its device address is looked up once per device
 // with that device current; host code uses only that address, never the array's name.
-constexpr size_t kScratchBytes = (size_t)8 << 20;
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -724,20 +753,9 @@ static ConvGemmArgs halo_dgrad_args(const ConvDesc& d, const void* src, int64_t 
   return g;
 }
 
-numbat_status numbat_conv_bwd_data(const numbat_conv_problem* p, const void* dy, const void* w, void* dx,
-                                   int accumulate, void* ws, size_t ws_bytes, void* stream) {
-  ConvDesc d;
-  numbat_status st = check_conv(p, &d);
-  if (st != NUMBAT_OK) return st;
-  if (dy == nullptr || w == nullptr || dx == nullptr) return fail(NUMBAT_ERR_NULL, "dy, w and dx are required");
-  if (!aligned16(dy)) return fail(NUMBAT_ERR_ALIGN, "dy must be 16-byte aligned");
-  if ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(dx)) & 1u)
-    return fail(NUMBAT_ERR_ALIGN, "w and dx must be 2-byte aligned");
-  if (d.ci % 8 == 0 && !aligned16(dx)) return fail(NUMBAT_ERR_ALIGN, "dx must be 16-byte aligned");
-  st = check_ws(ws, ws_bytes, with_header(bwd_data_ws(d)));
-  if (st != NUMBAT_OK) return st;
-  ws = ws_body(ws);
-
+// the data gradient's launches, once every check has passed
+static numbat_status conv_bwd_data_launch(const ConvDesc& d, const void* dy, const void* w, void* dx, int accumulate,
+                                          void* ws, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (narrow(d)) {
@@ -765,8 +783,9 @@ numbat_status numbat_conv_bwd_data(const numbat_conv_problem* p, const void* dy,
     return ok();
   }
 
+  const TileCfg sp = split_tile(d, true);
   const TileCfg ht = halo_tile(d, d.co, d.ci, true);
-  if (ht.variant == kVariantHalo) {
+  if (sp.variant != kVariantSplit && ht.variant == kVariantHalo) {
     ConvGemmArgs g = halo_dgrad_args(d, dy, d.y_pix, w, dx, accumulate);
     e = convhalo_launch(g, ht, s, KC_CONV_DGRAD);
     if (e != hipSuccess) return hip_fail(e, "data-gradient launch");
@@ -862,7 +881,7 @@ numbat_status numbat_conv_bwd_data(const numbat_conv_problem* p, const void* dy,
       }
       if (g.nphase > 0 && (g.nphase == kMaxPhases || last)) {
         groups[ngroups] = g;
-        tiles[ngroups] = convgemm_pick(mmax, cpad, d.co, ktmax, g.nphase, true);
+        tiles[ngroups] = sp.variant == kVariantSplit ? sp : convgemm_pick(mmax, cpad, d.co, ktmax, g.nphase, true);
         ++ngroups;
         g.nphase = 0;
         mmax = 0;
@@ -895,6 +914,21 @@ numbat_status numbat_conv_bwd_data(const numbat_conv_problem* p, const void* dy,
   return ok();
 }
 
+numbat_status numbat_conv_bwd_data(const numbat_conv_problem* p, const void* dy, const void* w, void* dx,
+                                   int accumulate, void* ws, size_t ws_bytes, void* stream) {
+  ConvDesc d;
+  numbat_status st = check_conv(p, &d);
+  if (st != NUMBAT_OK) return st;
+  if (dy == nullptr || w == nullptr || dx == nullptr) return fail(NUMBAT_ERR_NULL, "dy, w and dx are required");
+  if (!aligned16(dy)) return fail(NUMBAT_ERR_ALIGN, "dy must be 16-byte aligned");
+  if ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(dx)) & 1u)
+    return fail(NUMBAT_ERR_ALIGN, "w and dx must be 2-byte aligned");
+  if (d.ci % 8 == 0 && !aligned16(dx)) return fail(NUMBAT_ERR_ALIGN, "dx must be 16-byte aligned");
+  st = check_ws(ws, ws_bytes, with_header(bwd_data_ws(d)));
+  if (st != NUMBAT_OK) return st;
+  return conv_bwd_data_launch(d, dy, w, dx, accumulate, ws_body(ws), stream);
+}
+
 numbat_status numbat_conv_bwd_data_bn_silu_prologue(const numbat_conv_problem* p, const void* g,
                                                     int64_t g_pixel_stride, const void* y, const float* save_mean,
                                                     const float* save_rstd, const float* gamma, const float* beta,
@@ -921,6 +955,21 @@ numbat_status numbat_conv_bwd_data_bn_silu_prologue(const numbat_conv_problem* p
        reinterpret_cast<uintptr_t>(gamma) | reinterpret_cast<uintptr_t>(beta) | reinterpret_cast<uintptr_t>(dgamma) |
        reinterpret_cast<uintptr_t>(dbeta)) & 3u)
     return fail(NUMBAT_ERR_ALIGN, "save_mean, save_rstd, gamma, beta, dgamma and dbeta must be 4-byte aligned");
+  if (split_tile(d, true).variant == kVariantSplit) {
+    // where the data gradient runs on the reduction-splitting kernel: dy by the BN backward's
+    // apply, then that data gradient (it reads the weights in place and needs no workspace)
+    BnArgs b;
+    std::memset(&b, 0, sizeof b);
+    b.c = d.co;
+    b.m = d.m;
+    b.a_pix = g_pix;
+    b.y_pix = b.r_pix = b.dy_pix = d.y_pix;
+    const hipError_t e = bn_bwd_dy_launch(b, static_cast<const bf16_t*>(g), static_cast<const bf16_t*>(y), save_mean,
+                                          save_rstd, gamma, beta, static_cast<bf16_t*>(dy), dgamma, dbeta,
+                                          static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "BN+SiLU backward launch");
+    return conv_bwd_data_launch(d, dy, w, dx, accumulate, nullptr, stream);
+  }
   ConvGemmArgs a = halo_dgrad_args(d, g, g_pix, w, dx, accumulate);
   a.pro_kind = kProBwd;
   a.pro_gamma = gamma;

@@ -1755,7 +1755,7 @@ hipError_t launch_g(const ConvGemmArgs& a, int variant, hipStream_t s) {
     launch_dma<c.tm, c.tn, 3, 32, 4>(a, mmax, s);
   else if (variant == kVariantDma3W8 && c.tn <= 4)
     launch_dma<1, c.tn <= 4 ? c.tn : 4, 3, 64, 8>(a, mmax, s);
-#ifdef NUMBAT_TUNING
+#if defined(NUMBAT_TUNING) && NUMBAT_TUNING > 1
   else if (variant == 6)
     launch_dma<c.tm, c.tn, 4, 32, 4>(a, mmax, s);
   else if (variant == 8 && c.tn <= 4)
@@ -1793,7 +1793,9 @@ constexpr HInst kH[] = {
     {2, 2, 7, 1, 3, 0},   // 3: 256 x 64, W <= 95
     {2, 3, 6, 1, 3, 32},  // 4: 256 x 96 on 8 x 32 output pixels (a 10 x 34 halo), one tap per step
     {2, 2, 6, 1, 3, 32},  // 5: 256 x 64 on 8 x 32
-#ifdef NUMBAT_TUNING
+    {1, 3, 5, 3, 2, 0},   // 6: 128 x 96, W <= 95, a tap row per step (small grids)
+    {1, 2, 5, 3, 2, 0},   // 7: 128 x 64, W <= 95
+#if defined(NUMBAT_TUNING) && NUMBAT_TUNING > 1
     {1, 3, 4, 1, 3, 0},   // 6..
     {1, 3, 5, 1, 3, 0},
     {2, 3, 6, 1, 3, 0},
@@ -1829,7 +1831,7 @@ hipError_t launch_h(const ConvGemmArgs& a, hipStream_t s) {
     // the prologue's per-channel constants (dynamic LDS, sized to the channels so that the
     // blocks per CU stay those of the plain kernel wherever the channels allow)
     const size_t fwd_smem = (size_t)2 * a.cs * sizeof(float), bwd_smem = (size_t)4 * a.cs * sizeof(float);
-#ifdef NUMBAT_TUNING
+#if defined(NUMBAT_TUNING) && NUMBAT_TUNING > 1
     if (KV == 2 && getenv("NUMBAT_HALO_KV1") && a.pro_kind != kProBwd) {
       if (a.bt)
         NUMBAT_LAUNCH((convhalo_kernel<c.tm, c.tn, c.hi, c.kt, c.sb, true, c.tc, kProNone, 1>), grid, dim3(256), 0, s, a);
@@ -1866,11 +1868,21 @@ hipError_t launch_h_id(int id, const ConvGemmArgs& a, hipStream_t s) {
 int tap_dh(int32_t off) { return (int)(int16_t)(off & 0xffff); }
 int tap_dw(int32_t off) { return off >> 16; }
 
+// Source channels the direct-to-LDS kernel takes: multiples of 8 (a lane's 16-byte chunk never
+// splits a tap) of which a step crosses at most two taps (at least 16 channels for 32-deep
+// steps, 32 for 64-deep ones).
+bool dma_channels(int cs, int variant) { return cs % 8 == 0 && cs >= (variant == kVariantDma32 ? 16 : 32); }
+
 // Fills in the tap walk of the fast path (tw, toff0, cstep, rstep, halo_px) and reports
-// whether the fast path applies: 16-multiple source channels (at least 32), taps forming a grid with
+// whether the fast path applies: the kernel's channel counts, taps forming a grid with
 // unit steps, and every gathered byte of a tile within 32-bit buffer offsets.
-bool prepare_fast(ConvGemmArgs& a, int bm) {
-  if (a.cs % 16 != 0 || a.cs < 32) return false;
+bool prepare_fast(ConvGemmArgs& a, const TileCfg& t) {
+  return dma_channels(a.cs, t.variant) && convgemm_taps(a, t.bm);
+}
+
+}  // namespace
+
+bool convgemm_taps(ConvGemmArgs& a, int bm) {
   const int64_t pix2 = a.src_pix * 2;
   int halo = 0;
   for (int p = 0; p < a.nphase; ++p) {
@@ -1914,8 +1926,6 @@ bool prepare_fast(ConvGemmArgs& a, int bm) {
   return worst < (int64_t)kOob - (1 << 24);
 }
 
-}  // namespace
-
 // Tile and kernel choice, fitted to timings of every (kernel, tile, stages) choice over
 // the forward and data-gradient GEMMs of the detector's layers at batch 16, weighted by
 // how often each shape occurs (within 1% of the per-layer best in total):
@@ -1936,7 +1946,7 @@ bool prepare_fast(ConvGemmArgs& a, int bm) {
 //    stages of 64 when the grid holds 300 blocks or more, else three;
 //  * generic kernel (narrow or 8-multiple channels): 256-row tiles unless that leaves
 //    fewer than 512 blocks.
-TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, bool bt) {
+TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, bool bt, bool generic) {
   const int bns[4] = {128, 96, 64, 32};
   const int ncand = nout <= 32 ? 4 : 3;
   int bn = 128;
@@ -1948,7 +1958,7 @@ TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, boo
       bn = bns[i];
     }
   }
-  const bool fast = cs % 16 == 0 && cs >= 32;
+  const bool fast = !generic && dma_channels(cs, kVariantDma32);
   int bm, variant;
   if (fast && !bt) {
     const int64_t mt = (m_max + 127) / 128;
@@ -1996,8 +2006,13 @@ TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, boo
     }
   } else {
     const int64_t blocks256 = ((m_max + 255) / 256) * ((nout + bn - 1) / bn);
-    bm = blocks256 < 512 ? 128 : 256;
+    bm = blocks256 < 512 && !generic ? 128 : 256;
     variant = kVariantGeneric;
+  }
+  // fewer than 32 channels: a 64-deep step would cross more than two taps
+  if (fast && !dma_channels(cs, variant)) {
+    variant = kVariantDma32;
+    bm = 128;
   }
   int id = (bm == 128 ? 4 : 0) + (bn == 128 ? 0 : bn == 96 ? 1 : bn == 64 ? 2 : 3);
 #ifdef NUMBAT_TUNING
@@ -2044,12 +2059,14 @@ hipError_t convnarrow_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_
 }
 
 bool convgemm_direct(ConvGemmArgs a, const TileCfg& t) {
-  return t.variant != kVariantGeneric && prepare_fast(a, t.bm);
+  if (t.variant == kVariantSplit) return a.cs % 8 == 0 && convgemm_taps(a, t.bm);
+  return t.variant != kVariantGeneric && prepare_fast(a, t);
 }
 
 hipError_t convgemm_launch(ConvGemmArgs a, const TileCfg& t, hipStream_t s, int cls) {
+  if (t.variant == kVariantSplit) return convsplit_launch(a, t, s, cls);
   // a problem the fast paths cannot take runs the generic kernel on the same tile
-  const int variant = (t.variant != kVariantGeneric && prepare_fast(a, t.bm)) ? t.variant : kVariantGeneric;
+  const int variant = (t.variant != kVariantGeneric && prepare_fast(a, t)) ? t.variant : kVariantGeneric;
   if (a.bt && variant == kVariantGeneric) return hipErrorInvalidValue;  // needs K-major B
   a.remap = 0;
 #ifdef NUMBAT_TUNING
@@ -2071,10 +2088,10 @@ hipError_t convgemm_launch(ConvGemmArgs a, const TileCfg& t, hipStream_t s, int 
   return e;
 }
 
-// 3x3, stride 1, padding 1, 16-multiple source channels (at least 32), one phase
+// 3x3, stride 1, padding 1, 8-multiple source channels, one phase
 bool convhalo_shape(const ConvGemmArgs& a) {
   const GemmPhase& P = a.ph[0];
-  if (a.nphase != 1 || a.cs % 16 != 0 || a.cs < 32 || P.taps != 9 || a.gstride_h != 1 || a.gstride_w != 1 ||
+  if (a.nphase != 1 || a.cs % 8 != 0 || P.taps != 9 || a.gstride_h != 1 || a.gstride_w != 1 ||
       a.dstep_h != 1 || a.dstep_w != 1 || P.gh != a.hs || P.gw != a.ws || a.hd != a.hs || a.wd != a.ws)
     return false;
   if (!a.bt)
@@ -2091,8 +2108,8 @@ bool convhalo_shape(const ConvGemmArgs& a) {
 static int halo_pixels(int bm, int tc, int w) { return tc > 0 ? (bm / tc + 2) * (tc + 2) : bm + 2 * w + 2; }
 
 // Halo kernel tile, from a sweep of the instantiations over the detector's 3x3 stride-1
-// layers at batch 16 (each layer alone): 96 columns when 96 divides the channel count, else
-// 64; images up to 63 pixels wide on 128-row tiles with a whole tap row (three taps) per
+// layers at batch 16 (each layer alone): 96 columns unless 64 pad the channel count less;
+// images up to 63 pixels wide on 128-row tiles with a whole tap row (three taps) per
 // step and two weight stages (40 x 40, 192 channels: forward 33.6 -> 29.6 us, data
 // gradient 29.4 -> 24.0), up to 95 wide on 256-row tiles with one tap per step and three
 // stages (80 x 80, 96 channels: 35.4 -> 28.3 and 28.9 -> 22.6 us); wider images on
@@ -2101,17 +2118,27 @@ static int halo_pixels(int bm, int tc, int w) { return tc > 0 ? (bm / tc + 2) * 
 // data gradient 44.2 -> 39.3 us against the direct-to-LDS kernel; a linear tile of a
 // 160-wide image needs 2.5 image rows of halo and measured 30-80% slower, 4 x 32 tiles
 // with a tap row per step 10-20% slower, and 8 x 16 tiles on the 80-wide layers 13-18%
-// slower than their linear 256-row tiles).  Forward grids of fewer than 256 tiles (20 x 20,
-// 288 channels: 23.6 -> 26.1 us) keep the direct-to-LDS kernel.  Returns variant
-// kVariantGeneric when the halo kernel is not used.
-TileCfg convhalo_pick(int64_t m, int nout, int h, int w, bool bt, bool any_grid) {
-  const int tn = nout % 96 == 0 ? 3 : 2;
+// slower than their linear 256-row tiles).  Fewer than 160 256-row tiles leave CUs idle:
+// images of 64 to 95 columns then take 128-row tiles.  Forward grids of fewer than 256 tiles
+// keep the direct-to-LDS kernel on two-dimensional tiles and where 64 tiles or more walk a
+// long reduction (16 images of 20 x 20, 576 -> 192: 31.0 against 35.3 us; 288 -> 288: the
+// layer's training pass 96.2 against 101.7 us); elsewhere the halo kernel is as fast or
+// faster (one image of 40 x 40, 24 -> 72: 6.1 us, and 10.7 on the register-staged kernel; 4
+// of 26 x 26 x 128: 8.2 and 11.5; 8 of 40 x 40 x 192: 15.0 and 20.0).  Returns variant kVariantGeneric when the halo
+// kernel is not used.
+TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool any_grid) {
+  const int tn = (nout + 95) / 96 * 96 <= (nout + 63) / 64 * 64 ? 3 : 2;
+  const int64_t cols = (nout + 32 * tn - 1) / (32 * tn);
   int tm = w <= 63 ? 1 : 2, kt = w <= 63 ? 3 : 1, sb = w <= 63 ? 2 : 3, tc = 0;
   if (w > 95) {
     tm = 2;
     kt = 1;
     sb = 3;
     tc = 32;
+  } else if (w > 63 && (m + 255) / 256 * cols < 160) {
+    tm = 1;
+    kt = 3;
+    sb = 2;
   }
 #ifdef NUMBAT_TUNING
   if (const char* e = getenv("NUMBAT_HALO_TM")) tm = atoi(e);
@@ -2121,8 +2148,8 @@ TileCfg convhalo_pick(int64_t m, int nout, int h, int w, bool bt, bool any_grid)
 #endif
   const TileCfg none{0, 0, -1, kVariantGeneric};
   if (tc > 0 && (w % tc != 0 || (128 * tm) % tc != 0 || h % (128 * tm / tc) != 0)) return none;
-  const int64_t tiles = ((m + 128 * tm - 1) / (128 * tm)) * ((nout + 32 * tn - 1) / (32 * tn));
-  if (!bt && !any_grid && tiles < 256) return none;
+  const int64_t tiles = ((m + 128 * tm - 1) / (128 * tm)) * cols;
+  if (!bt && !any_grid && tiles < 256 && (tc > 0 || (cs >= 256 && tiles >= 64))) return none;
   int best = -1;
   for (int i = 0; i < kNumH; ++i) {
     const HInst& c = kH[i];

@@ -54,7 +54,8 @@ bool timing_events(hipEvent_t* start, hipEvent_t* stop);
 // into registers), and the direct-to-LDS kernel for 16-multiple channel counts of at least
 // 32 in its stage configurations (three or two stages, 32- or 64-element steps, four or
 // eight waves)
-enum { kVariantGeneric = 0, kVariantDma3 = 3, kVariantDma2 = 4, kVariantDma32 = 5, kVariantDma3W8 = 7, kVariantHalo = 11 };
+enum { kVariantGeneric = 0, kVariantDma3 = 3, kVariantDma2 = 4, kVariantDma32 = 5, kVariantDma3W8 = 7, kVariantHalo = 11,
+       kVariantSplit = 20 };
 struct TileCfg {
   int bm, bn;
   int id;       // instantiation id
@@ -141,20 +142,28 @@ constexpr int kProMaxC = 1024;  // most source channels the prologue stages cons
 enum { kPostNone = 0, kPostBias = 1, kPostBnSilu = 2 };
 // tile and kernel for a problem with at most m_max rows per phase, nout columns, cs
 // source channels, reduction length ktot and nphase phases; bt: the weights are read in
-// place (transposed B) if the direct-to-LDS kernel takes the problem
-TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, bool bt);
+// place (transposed B) if the direct-to-LDS kernel takes the problem; generic: the register-staged kernel
+TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, bool bt, bool generic = false);
 // a is taken by value: the launcher completes the tap-walk fields
 hipError_t convgemm_launch(ConvGemmArgs a, const TileCfg& t, hipStream_t s, int cls);
-// whether the direct-to-LDS kernel takes the problem on tile t (it can read B in place)
+// whether the direct-to-LDS or the reduction-splitting kernel takes the problem on tile t
+// (they can read B in place)
 bool convgemm_direct(ConvGemmArgs a, const TileCfg& t);
+// completes the tap-walk fields for tiles of bm rows; false when the taps form no grid or a
+// gathered byte or a weight lies beyond 31-bit offsets
+bool convgemm_taps(ConvGemmArgs& a, int bm);
+// problems with few tiles, on small tiles whose waves split the reduction (conv_split.hip):
+// convsplit_pick returns variant kVariantGeneric where another kernel is the better one
+TileCfg convsplit_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, bool bt);
+hipError_t convsplit_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_t s, int cls);
 // 3x3, stride-1, padding-1 convolutions whose input halo is staged in LDS once per
 // 32-channel chunk (conv_gemm.hip, convhalo_kernel): the forward (K-major weights, taps in
 // off[]) and the data gradient (bt: the OHWI weights read in place, flipped; off[] unused).
 // convhalo_shape: whether the kernel takes the problem; convhalo_pick: its tile for m rows,
-// nout columns and an h x w image, bt for the data gradient, any_grid to take small forward
-// grids too (variant kVariantGeneric when the halo kernel is not the one to use).
+// nout columns, cs source channels and an h x w image, bt for the data gradient, any_grid to
+// take every forward grid (variant kVariantGeneric when the halo kernel is not the one to use).
 bool convhalo_shape(const ConvGemmArgs& a);
-TileCfg convhalo_pick(int64_t m, int nout, int h, int w, bool bt, bool any_grid = false);
+TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool any_grid = false);
 hipError_t convhalo_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_t s, int cls);
 // forward convolution of a narrow input (cs = ci < 8, one phase, wt = OHWI weights with
 // K = taps * ci packed densely); rows per tile and columns per tile of narrow_pick
@@ -252,7 +261,6 @@ hipError_t bn_fwd_launch(const BnArgs& a, const bf16_t* y, const float* mean, co
 hipError_t bn_bwd_launch(const BnArgs& a, const bf16_t* g, const bf16_t* y, const float* save_mean,
                          const float* save_rstd, const float* gamma, const float* beta, bf16_t* dy, float* dgamma,
                          float* dbeta, bf16_t* res_grad, float* part2, int nblocks, float* coef, hipStream_t s);
-
 // dy alone, from dgamma and dbeta as bn_bwd_launch formed them (no reduce, no finalize)
 hipError_t bn_bwd_dy_launch(const BnArgs& a, const bf16_t* g, const bf16_t* y, const float* save_mean,
                             const float* save_rstd, const float* gamma, const float* beta, bf16_t* dy,

@@ -1,0 +1,157 @@
+"""GPU parity where the choice of kernel or tile turns on the size of the grid or on the
+channel count: small grids whose waves split the reduction (32 x 32, 32 x 64 and 64 x 64
+tiles), 8-multiple channel counts on the halo and direct-to-LDS kernels, 128-row halo tiles
+of 64 to 95 columns, weight-gradient patches and channel chunks that pass the image or the
+channels, and short pixel splits.  Against the fp64 oracle, rel_inf <= 2e-2 (bf16 outputs and
+gradients) and the statistics' own bound."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import ConvShape
+from parity import Inputs, assert_close, assert_stats, f64
+from paper_2609_10632_amd import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+if torch.cuda.is_available():
+    from paper_2609_10632_amd import blocks
+    from paper_2609_10632_amd import numbat as nb
+
+EPS = 1e-3
+# n, h, w, ci, co, k, s
+CASES = [
+    # reduction-splitting forward: 32 x 32 tiles (a ragged row and column tile; a reduction that
+    # ends mid-step; 1x1; stride 2), 32 x 64, 64 x 64
+    (1, 20, 20, 576, 72, 3, 1), (1, 9, 7, 120, 40, 3, 1), (2, 5, 5, 1152, 64, 1, 1), (1, 13, 17, 136, 48, 3, 2),
+    (3, 28, 28, 200, 136, 3, 1), (5, 28, 28, 264, 136, 3, 1),
+    # ... data gradient: 32 x 32 tiles at stride 1 (the plain case and c_out that ends a
+    # chunk early) and over four stride phases, 64 x 64 over four phases
+    (1, 12, 10, 40, 288, 3, 1), (1, 11, 11, 24, 136, 3, 1), (1, 13, 17, 40, 272, 3, 2), (1, 34, 30, 264, 576, 3, 2),
+    # 8-multiple channel counts: halo (one chunk and a tail, 8 channels, 128-row tiles of 70
+    # columns, two-dimensional tiles), direct-to-LDS (1x1, stride 2, more than 32768 rows)
+    (2, 30, 30, 24, 72, 3, 1), (2, 12, 62, 8, 16, 3, 1), (1, 21, 70, 40, 56, 3, 1), (1, 64, 96, 24, 40, 3, 1),
+    (2, 35, 35, 104, 80, 1, 1), (2, 31, 29, 24, 40, 3, 2), (2, 140, 130, 24, 56, 1, 1), (2, 19, 17, 56, 88, 1, 1),
+    # 96-column halo tiles for 80 channels
+    (2, 33, 41, 64, 80, 3, 1),
+    # patch-staged weight gradient past the image and the channels: 52 x 52 on 20 x 4, 13 x 37,
+    # 72 of 96 and 40 of 64 rows; 1x1 chunks of which the last ends early
+    (2, 52, 52, 64, 80, 3, 1), (2, 31, 45, 88, 72, 3, 1), (3, 18, 31, 144, 40, 3, 1), (2, 9, 31, 280, 48, 1, 1),
+    # the general weight gradient on splits of 4 steps
+    (2, 32, 32, 16, 32, 3, 1), (1, 60, 61, 16, 24, 3, 2),
+]
+IDS = ["n{}h{}w{}ci{}co{}k{}s{}".format(*c) for c in CASES]
+
+
+@pytest.mark.parametrize("i", range(len(CASES)), ids=IDS)
+def test_conv_passes(i):
+    """Forward with statistics, data gradient (plain and accumulated) and weight gradient (plain
+    and accumulated) on channel slices of wider tensors, whose other channels stay as they were."""
+    n, h, w, ci, co, k, st = CASES[i]
+    s = ConvShape(n, h, w, ci, co, k, k, st, st, k // 2, k // 2)
+    ip = Inputs(140, i)
+    xp, yp = ci + 16, co + 8
+    xb, dyb = ip.normal((n, h, w, xp), synth.T_X), ip.normal((*s.y_shape[:3], yp), synth.T_DY)
+    d0, wb = ip.normal((n, h, w, xp), synth.T_RES), ip.weight(co, k, ci)
+    blk = blocks.ConvBlock(n, h, w, ci, co, k, st, x_pixel_stride=xp, y_pixel_stride=yp)
+    ws = blocks.workspace(blk.ws_bytes())
+    x, dy, wt = blocks.dev_bf16(xb)[..., 16:], blocks.dev_bf16(dyb)[..., 8:], blocks.dev_bf16(wb)
+    y = torch.full((*s.y_shape[:3], yp), 7.0, dtype=torch.bfloat16, device="cuda")
+    stats = torch.empty(2 * co, device="cuda")
+    dx, dxa = torch.full((n, h, w, xp), 7.0, dtype=torch.bfloat16, device="cuda"), blocks.dev_bf16(d0)
+    dw = torch.full(s.w_shape, float("nan"), device="cuda")
+    nb.numbat_conv_fwd(blk.prob, x, wt, y[..., 8:], stats, ws)
+    nb.numbat_conv_bwd_data(blk.prob, dy, wt, dx[..., 16:], False, ws)
+    nb.numbat_conv_bwd_data(blk.prob, dy, wt, dxa[..., 16:], True, ws)
+    nb.numbat_conv_bwd_weight(blk.prob, x, dy, dw, False, ws)
+    dwa = dw.clone()
+    nb.numbat_conv_bwd_weight(blk.prob, x, dy, dwa, True, ws)
+    torch.cuda.synchronize()
+    x64, dy64, w64 = f64(xb[..., 16:]), f64(dyb[..., 8:]), f64(wb)
+    yref = oracle.conv_fwd(x64, w64, s)
+    got = blocks.host_f64(y)
+    assert_close(got[..., 8:], yref, "y")
+    assert np.all(got[..., :8] == 7.0)
+    mref, vref = oracle.bn_stats(yref)
+    sg = blocks.host_f64(stats)
+    assert_stats(sg[:co], sg[co:], mref, vref, EPS, "batch statistics")
+    dxref = oracle.conv_dgrad(dy64, w64, s)
+    got = blocks.host_f64(dx)
+    assert_close(got[..., 16:], dxref, "dx")
+    assert np.all(got[..., :16] == 7.0)
+    got = blocks.host_f64(dxa)
+    assert_close(got[..., 16:], dxref + f64(d0[..., 16:]), "dx accumulated")
+    assert np.array_equal(got[..., :16], f64(d0[..., :16]))
+    dwref = oracle.conv_wgrad(x64, dy64, s)
+    # fp32 sums: the weight gradient's own error is far below the bf16 bound
+    assert_close(blocks.host_f64(dw), dwref, "dw", 1e-5)
+    assert_close(blocks.host_f64(dwa), 2 * dwref, "dw accumulated", 1e-5)
+
+
+@pytest.mark.parametrize("i", [0, 1, 4, 5, 10], ids=[IDS[i] for i in (0, 1, 4, 5, 10)])
+def test_inference_outputs(i):
+    """The bias and the evaluation-mode BN + SiLU output stages on those tiles."""
+    n, h, w, ci, co, k, st = CASES[i]
+    s = ConvShape(n, h, w, ci, co, k, k, st, st, k // 2, k // 2)
+    ip = Inputs(141, i)
+    xb, wb = ip.normal(s.x_shape, synth.T_X), ip.weight(co, k, ci)
+    f = lambda a: a.astype(np.float64)
+    bias, g = ip.f32_normal((co,), synth.T_RES, 0.0, 0.5), ip.f32_uniform((co,), synth.T_GAMMA, 0.5, 1.5)
+    b, m, v = (ip.f32_normal((co,), synth.T_BETA, 0.0, 0.1), ip.f32_normal((co,), synth.T_MEAN, 0.0, 0.2),
+               ip.f32_uniform((co,), synth.T_VAR, 0.3, 2.0))
+    p = nb.conv_problem(n, h, w, ci, co, k, stride=st)
+    x, wt = blocks.dev_bf16(xb), blocks.dev_bf16(wb)
+    y1 = torch.empty(s.y_shape, dtype=torch.bfloat16, device="cuda")
+    y2 = torch.empty_like(y1)
+    nb.numbat_conv_fwd_bias(p, x, wt, blocks.dev_f32(bias), y1)
+    nb.numbat_conv_bn_silu_infer(p, x, wt, *(blocks.dev_f32(t) for t in (g, b, m, v)), EPS, y2)
+    torch.cuda.synchronize()
+    yref = oracle.conv_fwd(f64(xb), f64(wb), s)
+    assert_close(blocks.host_f64(y1), yref + f(bias), "conv + bias")
+    assert_close(blocks.host_f64(y2), oracle.bn_silu_eval(yref, f(m), f(v), f(g), f(b), EPS), "conv + eval BN + SiLU")
+
+
+# rows, channels: at most 4096 partials (the apply adds them itself) and just past it; one
+# partial; more channels than threads
+@pytest.mark.parametrize("m,c", [(65536, 32), (65537, 32), (300, 8), (784, 288), (785, 288), (16, 2048), (50, 264)])
+def test_bn_backward_folds_few_partials(m, c):
+    ip = Inputs(142, c)
+    yb, gb = ip.normal((m, c), synth.T_Y, 0.3, 2.0), ip.normal((m, c), synth.T_G)
+    gamma, beta = ip.f32_uniform((c,), synth.T_GAMMA, 0.5, 1.5), ip.f32_normal((c,), synth.T_BETA, 0.0, 0.3)
+    mean, var = oracle.bn_stats(f64(yb))
+    mean32, rstd32 = mean.astype(np.float32), (1 / np.sqrt(var + EPS)).astype(np.float32)
+    p = nb.bn_problem(m, c, EPS)
+    dy = torch.empty((m, c), dtype=torch.bfloat16, device="cuda")
+    dgamma, dbeta = torch.empty(c, device="cuda"), torch.empty(c, device="cuda")
+    ws = blocks.workspace(nb.numbat_workspace_size(nb.OP_BN_SILU_BWD, p))
+    dev = [blocks.dev_f32(t) for t in (mean32, rstd32, gamma, beta)]
+    nb.numbat_bn_silu_bwd(p, blocks.dev_bf16(gb), blocks.dev_bf16(yb), *dev, dy, dgamma, dbeta, None, ws=ws)
+    torch.cuda.synchronize()
+    ref = oracle.bn_silu_bwd(f64(gb), f64(yb), mean, var, gamma.astype(np.float64), beta.astype(np.float64), EPS)
+    for got, want, name in zip((dy, dgamma, dbeta), ref, ("dy", "dgamma", "dbeta")):
+        assert_close(blocks.host_f64(got), want, name)
+
+
+@pytest.mark.parametrize("shape", [(1, 20, 20, 288, 288), (1, 12, 10, 48, 288)])
+def test_backward_prologue_equals_the_two_calls_on_small_grids(shape):
+    """numbat_conv_bwd_data_bn_silu_prologue where the data gradient's waves split the reduction:
+    dx (accumulated) and dy equal numbat_bn_silu_bwd followed by numbat_conv_bwd_data bit for bit."""
+    n, h, w, ci, co = shape
+    ip = Inputs(143, ci)
+    blk = blocks.ConvBlock(n, h, w, ci, co, 3, 1)
+    g, y = blocks.dev_bf16(ip.normal((n, h, w, co + 8), synth.T_G)), blocks.dev_bf16(ip.normal((n, h, w, co), synth.T_Y))
+    wt, x0 = blocks.dev_bf16(ip.weight(co, 3, ci)), blocks.dev_bf16(ip.normal((n, h, w, ci), synth.T_RES))
+    mean, rstd, gamma, beta = (blocks.dev_f32(ip.f32_uniform((co,), t, 0.5, 1.5)) for t in
+                               (synth.T_MEAN, synth.T_VAR, synth.T_GAMMA, synth.T_BETA))
+    ws = blocks.workspace(blk.ws_bytes())
+    dy, dy2 = torch.empty_like(y), torch.empty_like(y)
+    dx, dx2 = x0.clone(), x0.clone()
+    dgamma, dbeta = torch.empty(co, device="cuda"), torch.empty(co, device="cuda")
+    bn = blk.bn(a_pixel_stride=co + 8)
+    nb.numbat_bn_silu_bwd(bn, g, y, mean, rstd, gamma, beta, dy, dgamma, dbeta, None, ws=ws)
+    nb.numbat_conv_bwd_data(blk.prob, dy, wt, dx, True, ws)
+    nb.numbat_conv_bwd_data_bn_silu_prologue(blk.prob, g, y, mean, rstd, gamma, beta, dgamma, dbeta, wt, dx2, dy2, True,
+                                             g_pixel_stride=co + 8)
+    torch.cuda.synchronize()
+    assert torch.equal(dy.view(torch.int16), dy2.view(torch.int16))
+    assert torch.equal(dx.view(torch.int16), dx2.view(torch.int16))

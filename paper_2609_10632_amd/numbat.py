@@ -139,14 +139,22 @@ def _nbytes(t) -> int:
     return t.numel() * t.element_size()
 
 
+_torch = None
+
+
 def _stream(stream) -> Optional[int]:
+    global _torch
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
-    import torch
-
-    if not torch.cuda.is_available():
+    if _torch is None:
+        import torch as _torch
+    if _torch.cuda.is_initialized():
+        # the raw handle of torch.cuda.current_stream(), without the Stream object around it
+        # (0.5 us a call instead of 3.5, of the 10.5 us a small call spends on the host)
+        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+    if not _torch.cuda.is_available():
         return None  # NULL stream; only validation failures can happen without a GPU
-    return torch.cuda.current_stream().cuda_stream
+    return _torch.cuda.current_stream().cuda_stream
 
 
 def _check(status: int, call: str) -> None:

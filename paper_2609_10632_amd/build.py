@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnumbat_conv.so")
-SOURCES = ["conv_gemm.hip", "conv_split.hip", "conv_aux.hip", "conv_wgrad.hip", "conv_wgrad_halo.hip", "bn_silu.hip", "optim.hip", "pool.hip", "abi.cpp"]
+SOURCES = ["conv_gemm.hip", "conv_halo.hip", "conv_split.hip", "conv_aux.hip", "conv_wgrad.hip", "conv_wgrad_halo.hip", "bn_silu.hip", "optim.hip", "pool.hip", "abi.cpp"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -31,7 +31,7 @@ def _compile(src: str) -> str:
 
 def build() -> str:
     os.makedirs(OUT_DIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp"
     # -z defs: a symbol left undefined (e.g. a kernel launch stub the host pass dropped)

@@ -187,13 +187,13 @@ bool halo_geometry(const ConvDesc& d) {
 #endif
   return on;
 }
-TileCfg halo_tile(const ConvDesc& d, int cs, int nout, bool bt) {
+TileCfg halo_tile(const ConvDesc& d, int cs, int nout, bool bt, bool pro_bwd = false) {
   const int64_t pix2 = (bt ? d.y_pix : d.x_pix) * 2;
   // (a tile's halo, of at most 256 + 2 w + 2 or 10 w + 34 pixels, within 31-bit byte offsets)
   if (!halo_geometry(d) || cs % 8 != 0 || (int64_t)nout * 9 * cs * 2 >= ((int64_t)1 << 31) - 16 ||
       (10ll * d.w + 258) * pix2 >= (1ll << 31) - (1ll << 25))
     return TileCfg{0, 0, -1, kVariantGeneric};
-  return convhalo_pick(d.m, nout, cs, d.h, d.w, bt);
+  return convhalo_pick(d.m, nout, cs, d.h, d.w, bt, false, pro_bwd);
 }
 
 // The reduction-splitting kernel's tile, where it is the one to run; its gathers address the
@@ -248,7 +248,7 @@ TileCfg prologue_tile(const ConvDesc& d) {
 // problem (kVariantGeneric when the kernel does not take it)
 TileCfg bwd_prologue_tile(const ConvDesc& d) {
   if (d.co > kProMaxC || d.co % 16 != 0 || d.co < 32 || narrow(d)) return TileCfg{0, 0, -1, kVariantGeneric};
-  return halo_tile(d, d.co, d.ci, true);
+  return halo_tile(d, d.co, d.ci, true, true);
 }
 
 // per-tile statistics partials, sized for the forward's tile and the prologue-fused

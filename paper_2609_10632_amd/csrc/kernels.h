@@ -51,11 +51,11 @@ bool timing_events(hipEvent_t* start, hipEvent_t* stop);
   } while (0)
 
 // conv GEMM kernel variants: generic (source channels a multiple of 8; A fragments loaded
-// into registers), and the direct-to-LDS kernel for 16-multiple channel counts of at least
-// 32 in its stage configurations (three or two stages, 32- or 64-element steps, four or
-// eight waves)
+// into registers), the direct-to-LDS kernel in its stage configurations (three or two stages,
+// 32- or 64-element steps, four or eight waves) and on wide tiles (eight waves, four rows of
+// two), the halo kernel, and the kernel whose waves split the reduction
 enum { kVariantGeneric = 0, kVariantDma3 = 3, kVariantDma2 = 4, kVariantDma32 = 5, kVariantDma3W8 = 7, kVariantHalo = 11,
-       kVariantSplit = 20 };
+       kVariantWide = 12, kVariantSplit = 20 };
 struct TileCfg {
   int bm, bn;
   int id;       // instantiation id
@@ -161,9 +161,10 @@ hipError_t convsplit_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_t
 // off[]) and the data gradient (bt: the OHWI weights read in place, flipped; off[] unused).
 // convhalo_shape: whether the kernel takes the problem; convhalo_pick: its tile for m rows,
 // nout columns, cs source channels and an h x w image, bt for the data gradient, any_grid to
-// take every forward grid (variant kVariantGeneric when the halo kernel is not the one to use).
+// take every forward grid, pro_bwd for the backward prologue (variant kVariantGeneric when the halo kernel is not the one to use).
 bool convhalo_shape(const ConvGemmArgs& a);
-TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool any_grid = false);
+TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool any_grid = false,
+                      bool pro_bwd = false);
 hipError_t convhalo_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_t s, int cls);
 // forward convolution of a narrow input (cs = ci < 8, one phase, wt = OHWI weights with
 // K = taps * ci packed densely); rows per tile and columns per tile of narrow_pick

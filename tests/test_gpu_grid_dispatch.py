@@ -1,5 +1,5 @@
 """GPU parity where the choice of kernel or tile turns on the size of the grid or on the
-channel count: small grids whose waves split the reduction (32 x 32, 32 x 64 and 64 x 64
+channel count: eight-wave tiles on grids that fill rounds of the GPU; small grids whose waves split the reduction (32 x 32, 32 x 64 and 64 x 64
 tiles), 8-multiple channel counts on the halo and direct-to-LDS kernels, 128-row halo tiles
 of 64 to 95 columns, weight-gradient patches and channel chunks that pass the image or the
 channels, and short pixel splits.  Against the fp64 oracle, rel_inf <= 2e-2 (bf16 outputs and
@@ -39,6 +39,13 @@ CASES = [
     (2, 52, 52, 64, 80, 3, 1), (2, 31, 45, 88, 72, 3, 1), (3, 18, 31, 144, 40, 3, 1), (2, 9, 31, 280, 48, 1, 1),
     # the general weight gradient on splits of 4 steps
     (2, 32, 32, 16, 32, 3, 1), (1, 60, 61, 16, 24, 3, 2),
+    # eight-wave halo tiles of 256 rows, forward or data gradient: up to 63 columns, 64 to 95, and
+    # two-dimensional; a last chunk of 8 or 16 channels, a ragged last row tile
+    (9, 40, 41, 48, 288, 3, 1), (9, 40, 41, 288, 40, 3, 1), (3, 70, 71, 40, 288, 3, 1), (3, 70, 71, 288, 48, 3, 1),
+    (8, 160, 160, 16, 64, 3, 1),
+    # eight-wave direct-to-LDS tiles: 256 x 192, 256 x 128 (1x1 and stride 2) and 128 x 128
+    (5, 57, 57, 264, 576, 1, 1), (5, 60, 60, 576, 40, 1, 1), (5, 75, 75, 256, 248, 1, 1), (10, 95, 94, 40, 248, 3, 2),
+    (3, 37, 37, 72, 576, 1, 1), (2, 50, 58, 640, 48, 1, 1),
 ]
 IDS = ["n{}h{}w{}ci{}co{}k{}s{}".format(*c) for c in CASES]
 
@@ -132,10 +139,12 @@ def test_bn_backward_folds_few_partials(m, c):
         assert_close(blocks.host_f64(got), want, name)
 
 
-@pytest.mark.parametrize("shape", [(1, 20, 20, 288, 288), (1, 12, 10, 48, 288)])
-def test_backward_prologue_equals_the_two_calls_on_small_grids(shape):
-    """numbat_conv_bwd_data_bn_silu_prologue where the data gradient's waves split the reduction:
-    dx (accumulated) and dy equal numbat_bn_silu_bwd followed by numbat_conv_bwd_data bit for bit."""
+@pytest.mark.parametrize("shape", [(1, 20, 20, 288, 288), (1, 12, 10, 48, 288), (9, 40, 41, 288, 48),
+                                   (3, 70, 71, 288, 48), (8, 160, 160, 64, 48)])
+def test_backward_prologue_equals_the_two_calls(shape):
+    """numbat_conv_bwd_data_bn_silu_prologue where the data gradient's waves split the reduction
+    or run on eight-wave halo tiles: dx (accumulated) and dy equal numbat_bn_silu_bwd followed by
+    numbat_conv_bwd_data bit for bit."""
     n, h, w, ci, co = shape
     ip = Inputs(143, ci)
     blk = blocks.ConvBlock(n, h, w, ci, co, 3, 1)
@@ -155,3 +164,26 @@ def test_backward_prologue_equals_the_two_calls_on_small_grids(shape):
     torch.cuda.synchronize()
     assert torch.equal(dy.view(torch.int16), dy2.view(torch.int16))
     assert torch.equal(dx.view(torch.int16), dx2.view(torch.int16))
+
+
+@pytest.mark.parametrize("shape", [(9, 40, 41, 48, 288), (3, 70, 71, 48, 288), (8, 160, 160, 48, 64)])
+def test_forward_prologue_equals_the_two_calls(shape):
+    """numbat_conv_fwd_bn_silu_prologue on eight-wave halo tiles: y and the batch statistics equal
+    numbat_bn_silu_fwd followed by numbat_conv_fwd bit for bit."""
+    n, h, w, ci, co = shape
+    ip = Inputs(144, ci)
+    blk = blocks.ConvBlock(n, h, w, ci, co, 3, 1)
+    y0, wt = blocks.dev_bf16(ip.normal((n, h, w, ci), synth.T_Y)), blocks.dev_bf16(ip.weight(co, 3, ci))
+    stats0 = blocks.dev_f32(ip.f32_uniform((2 * ci,), synth.T_VAR, 0.3, 2.0))
+    gamma = blocks.dev_f32(ip.f32_uniform((ci,), synth.T_GAMMA, 0.5, 1.5))
+    beta = blocks.dev_f32(ip.f32_normal((ci,), synth.T_BETA, 0.0, 0.3))
+    ws = blocks.workspace(max(blk.ws_bytes(), 256))
+    a, sm, sr = torch.empty_like(y0), torch.empty(ci, device="cuda"), torch.empty(ci, device="cuda")
+    y = [torch.empty((n, h, w, co), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    st = [torch.empty(2 * co, device="cuda") for _ in range(2)]
+    nb.numbat_bn_silu_fwd(nb.bn_problem(n * h * w, ci, EPS), y0, stats0, gamma, beta, None, a, sm, sr, ws=ws)
+    nb.numbat_conv_fwd(blk.prob, a, wt, y[0], st[0], ws)
+    nb.numbat_conv_fwd_bn_silu_prologue(blk.prob, y0, stats0, gamma, beta, EPS, wt, y[1], st[1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(y[0].view(torch.int16), y[1].view(torch.int16))
+    assert torch.equal(st[0].view(torch.int32), st[1].view(torch.int32))

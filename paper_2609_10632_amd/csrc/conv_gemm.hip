@@ -5,7 +5,8 @@
 // Kernels:
 //  * convdma_kernel, for source channel counts that are multiples of 8 and at least 16 (every
 //    layer of the detector but the image input): both operands reach LDS through loads that
-//    write LDS directly, in 2 to 4 stages (up to 6 supported), with 4 or 8 waves split along M;
+//    write LDS directly, in 2 to 4 stages (up to 6 supported), with 4 or 8 waves split along M or, on tiles of up to
+//    256 x 192 outputs, eight waves in four rows of two;
 //  * convgemm_kernel, for any other channel count that is a multiple of 8 (and tiles
 //    whose address span exceeds 31 bits): each wave loads its own MFMA A fragments (16
 //    contiguous bytes per lane) from global memory into a register ring several steps
@@ -946,6 +947,45 @@ bool convgemm_taps(ConvGemmArgs& a, int bm) {
   return worst < (int64_t)kOob - (1 << 24);
 }
 
+// Eight-wave tiles whose waves stand in four rows of two: a wave's share of a 256 x 192 tile is
+// 64 x 96 (5 LDS fragments per 6 products), and a CU loads 448 rows per 49152 products where 128
+// x 64 tiles load 192 per 8192: the loads into LDS, which bound the other tiles, fall behind
+// the products.  One block per CU, so the grid has to fill whole rounds of 256 blocks: the
+// tile is taken where the GEMM's own area is at least a share `eff` of the rounds' area and
+// nout fills its columns to 10%.  Measured, us, against the rule below it:
+//  forward (eff 0.6, reductions of 256 or more): 16 x 40 x 40, 960 -> 384 (0.78) 33.7 -> 29.0, 80 x
+//   80, 576 -> 192 (0.78) 63.4 -> 48.2, 160 x 160 stride 2, 96 -> 192 (0.78) 64.5 -> 55.9; 12 x 52 x 52 x
+//   256 on 256 x 128 (0.99) 17.8 -> 12.1, 100 x 100 stride 2, 64 -> 128 (0.61) 19.6 -> 14.0; 40 x 40 x 320
+//   (0.65, a sixth of the columns idle) 15.1 -> 16.4.  Short reductions are bound by memory, and
+//   one block per CU overlaps its output with nothing: training passes of 80 x 80 x 192 148.8
+//   -> 150.8, 32 images of 80 x 80 x 128 170.2 -> 175.3
+//  data gradient (eff 0.8, at most two rounds; the weights' transposing reads cost more): 40 x
+//   40, 960 <- 384 (0.98) 35.6 -> 33.1, 52 x 52 x 256 (0.99) 14.5 -> 10.7; 40 x 40, 768 <- 384 (0.78) 28.8 ->
+//   30.2; six rounds, 4 x 125 x 144, 624 <- 272, the training pass 283.9 -> 287.4
+//  128 x 128 tiles, for one round of at least 140 (data gradient 225) blocks: 20 x 20, 1152 -> 576
+//   (250) 18.6 -> 14.9, 40 x 40 stride 2, 384 -> 576 (250) 37.7 -> 33.7, 26 x 26, 512 -> 256 (170) 12.5 -> 9.8; 8
+//   x 26 x 26 (86) 9.4 -> 10.0.
+enum { kWide256x192 = 0, kWide256x128 = 1, kWide128x128 = 4 };  // (generic tiles of as many rows have these ids)
+TileCfg wide_pick(int64_t m, int nout, int ktot, bool bt) {
+  TileCfg best{0, 0, -1, kVariantGeneric};
+  double best_eff = bt ? 0.8 : 0.6;
+  constexpr int kT[2][3] = {{256, 192, kWide256x192}, {256, 128, kWide256x128}};
+  for (const auto& t : kT) {
+    const int64_t cols = (nout + t[1] - 1) / t[1], tiles = (m + t[0] - 1) / t[0] * cols, rounds = (tiles + 255) / 256;
+    if (cols * t[1] * 10 > (int64_t)nout * 11 || (bt ? rounds > 2 : ktot < 256)) continue;
+    const double eff = (double)m * nout / ((double)rounds * 256 * t[0] * t[1]);
+    if (eff >= best_eff) {
+      best_eff = eff;
+      best = TileCfg{t[0], t[1], t[2], kVariantWide};
+    }
+  }
+  if (best.variant == kVariantWide) return best;
+  const int64_t cols = (nout + 127) / 128, tiles = (m + 127) / 128 * cols;
+  if (tiles <= 256 && tiles >= (bt ? 225 : 140) && cols * 1280 <= (int64_t)nout * 12 && m <= 16384)
+    return TileCfg{128, 128, kWide128x128, kVariantWide};
+  return best;
+}
+
 // Tile and kernel choice, fitted to timings of every (kernel, tile, stages) choice over
 // the forward and data-gradient GEMMs of the detector's layers at batch 16, weighted by
 // how often each shape occurs (within 1% of the per-layer best in total):
@@ -979,6 +1019,10 @@ TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, boo
     }
   }
   const bool fast = !generic && dma_channels(cs, kVariantDma32);
+  if (fast && cs >= 32 && nphase == 1) {
+    const TileCfg t = wide_pick(m_max, nout, ktot, bt);
+    if (t.variant == kVariantWide) return t;
+  }
   int bm, variant;
   if (fast && !bt) {
     const int64_t mt = (m_max + 127) / 128;
@@ -1084,6 +1128,16 @@ hipError_t convgemm_launch(ConvGemmArgs a, const TileCfg& t, hipStream_t s, int 
 #ifdef NUMBAT_TUNING
   if (const char* e = getenv("NUMBAT_REMAP_CONV")) a.remap = atoi(e);
 #endif
+  if (variant == kVariantWide) {
+    int mmax = 0;
+    for (int p = 0; p < a.nphase; ++p) mmax = a.ph[p].m > mmax ? a.ph[p].m : mmax;
+    trace_begin(cls);
+    if (t.id == kWide256x192) launch_dma<2, 3, 4, 32, 8, 2>(a, mmax, s);
+    else if (t.id == kWide256x128) launch_dma<2, 2, 4, 32, 8, 2>(a, mmax, s);
+    else launch_dma<1, 2, 3, 64, 8, 2>(a, mmax, s);
+    trace_end(cls);
+    return hipGetLastError();
+  }
   trace_begin(cls);
   hipError_t e;
   switch (t.id) {

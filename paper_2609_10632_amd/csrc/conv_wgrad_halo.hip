@@ -420,9 +420,9 @@ int wh_ob(int co) {
 
 // Whether a configuration that pads channels or pixels (`pixels` staged in all) is still the
 // one to run: it executes at most kPadMost times the products of the general kernel, whose
-// tiles pad kh kw c_in to 128 columns.  Per product this kernel is 15-35% faster (8 x 52 x 52,
-// 192 -> 80 on 20 x 4 patches, 15% of them outside the image: 27.3 -> 22.3 us; 12 x 13 x 13 x
-// 256 18.1 -> 14.7; 16 x 33 x 33 x 80 18.1 -> 12.7).
+// tiles pad kh kw c_in to 128 columns.  It reads each input element about 1.4 times where the
+// general kernel gathers it per tap: 8 x 52 x 52, 192 -> 80 on 20 x 4 patches, 15% of them outside
+// the image, 27.3 -> 22.3 us; 5 x 45 x 48 x 256 29.8 -> 28.8.
 constexpr double kPadMost = 1.15;
 bool wh_cheaper(const WgradArgs& a, const WhCfg& c, int64_t pixels) {
   auto up = [](int64_t v, int64_t q) { return (v + q - 1) / q * q; };

@@ -31,7 +31,7 @@ CASES = [
     # 8-multiple channel counts: halo (one chunk and a tail, 8 channels, 128-row tiles of 70
     # columns, two-dimensional tiles), direct-to-LDS (1x1, stride 2, more than 32768 rows)
     (2, 30, 30, 24, 72, 3, 1), (2, 12, 62, 8, 16, 3, 1), (1, 21, 70, 40, 56, 3, 1), (1, 64, 96, 24, 40, 3, 1),
-    (2, 35, 35, 104, 80, 1, 1), (2, 31, 29, 24, 40, 3, 2), (2, 140, 130, 24, 56, 1, 1), (2, 19, 17, 56, 88, 1, 1),
+    (2, 35, 35, 104, 80, 1, 1), (2, 31, 29, 24, 40, 3, 2), (4, 190, 190, 88, 24, 3, 2), (2, 140, 130, 24, 56, 1, 1), (2, 19, 17, 56, 88, 1, 1),
     # 96-column halo tiles for 80 channels
     (2, 33, 41, 64, 80, 3, 1),
     # patch-staged weight gradient past the image and the channels: 52 x 52 on 20 x 4, 13 x 37,

@@ -196,21 +196,159 @@ TileCfg halo_tile(const ConvDesc& d, int cs, int nout, bool bt, bool pro_bwd = f
   return convhalo_pick(d.m, nout, cs, d.h, d.w, bt, false, pro_bwd);
 }
 
-// The reduction-splitting kernel's tile, where it is the one to run; its gathers address the
-// whole tensor with 31-bit byte offsets.
+// the geometry of the forward's GEMM (pointers and output options are the launch's)
+ConvGemmArgs fwd_geometry(const ConvDesc& d) {
+  ConvGemmArgs g;
+  std::memset(&g, 0, sizeof g);
+  g.src_pix = d.x_pix;
+  g.hs = d.h;
+  g.ws = d.w;
+  g.cs = d.ci;
+  g.nout = d.co;
+  g.nimg = d.n;
+  g.gstride_h = d.sh;
+  g.gstride_w = d.sw;
+  g.dst_pix = d.y_pix;
+  g.hd = d.ho;
+  g.wd = d.wo;
+  g.dstep_h = g.dstep_w = 1;
+  g.nphase = 1;
+  GemmPhase& P = g.ph[0];
+  P.taps = d.kh * d.kw;
+  P.ktot = P.taps * d.ci;
+  P.gh = d.ho;
+  P.gw = d.wo;
+  P.m = (int32_t)d.m;
+  P.div_gw = make_fastdiv((uint32_t)d.wo);
+  P.div_ghw = make_fastdiv((uint32_t)(d.ho * d.wo));
+  for (int r = 0; r < d.kh; ++r)
+    for (int q = 0; q < d.kw; ++q)
+      P.off[r * d.kw + q] = (int32_t)((uint32_t)(uint16_t)(int16_t)(r - d.ph) | ((uint32_t)(q - d.pw) << 16));
+  return g;
+}
+
+// The geometry of the data gradient's GEMMs: the stride phases (strides are at most 4), and the
+// launches of up to kMaxPhases of them (blockIdx.z = phase); phases without pixels are in none.
+struct DgradGemms {
+  PhaseTaps ph[16];
+  int first[16];  // weight columns (taps * c_in * c_out) before the phase's in the re-laid-out copy
+  int nphase;
+  ConvGemmArgs groups[4];
+  int of[4][kMaxPhases];  // the stride phase of each group's phases
+  int64_t mmax[4];
+  int ktmax[4];
+  int ngroups;
+};
+void dgrad_geometry(const ConvDesc& d, DgradGemms* out) {
+  // stride phases (a, b): input rows h = a + sh*i read output rows p = i + (a + ph - r) / sh
+  int nphase = 0, total = 0;
+  int offh[16][kMaxTaps], offw[16][kMaxTaps];
+  for (int pa = 0; pa < d.sh; ++pa)
+    for (int pb = 0; pb < d.sw; ++pb) {
+      PhaseTaps& f = out->ph[nphase];
+      f.count = 0;
+      for (int r = 0; r < d.kh; ++r) {
+        const int th = pa + d.ph - r;
+        if (((th % d.sh) + d.sh) % d.sh != 0) continue;
+        for (int s = 0; s < d.kw; ++s) {
+          const int tw = pb + d.pw - s;
+          if (((tw % d.sw) + d.sw) % d.sw != 0) continue;
+          f.r[f.count] = r;
+          f.s[f.count] = s;
+          offh[nphase][f.count] = (th - ((th % d.sh) + d.sh) % d.sh) / d.sh;  // exact
+          offw[nphase][f.count] = (tw - ((tw % d.sw) + d.sw) % d.sw) / d.sw;
+          ++f.count;
+        }
+      }
+      out->first[nphase] = total * d.ci * d.co;
+      total += f.count;
+      ++nphase;
+    }
+  out->nphase = nphase;
+  ConvGemmArgs g;
+  std::memset(&g, 0, sizeof g);
+  g.src_pix = d.y_pix;
+  g.hs = d.ho;
+  g.ws = d.wo;
+  g.cs = d.co;
+  g.nout = d.ci;
+  g.nimg = d.n;
+  g.gstride_h = g.gstride_w = 1;
+  g.dst_pix = d.x_pix;
+  g.hd = d.h;
+  g.wd = d.w;
+  g.dstep_h = d.sh;
+  g.dstep_w = d.sw;
+  out->ngroups = 0;
+  int f = 0;
+  int64_t mmax = 0;
+  int ktmax = 0;
+  const int64_t wpix2 = (int64_t)d.ci * 2;
+  for (int pa = 0; pa < d.sh; ++pa)
+    for (int pb = 0; pb < d.sw; ++pb, ++f) {
+      const int gh = pa < d.h ? (d.h - pa + d.sh - 1) / d.sh : 0;
+      const int gw = pb < d.w ? (d.w - pb + d.sw - 1) / d.sw : 0;
+      const bool last = (pa == d.sh - 1 && pb == d.sw - 1);
+      if (gh > 0 && gw > 0) {
+        out->of[out->ngroups][g.nphase] = f;
+        GemmPhase& P = g.ph[g.nphase++];
+        const PhaseTaps& T = out->ph[f];
+        P.taps = T.count;
+        P.ktot = P.taps * d.co;
+        P.gh = gh;
+        P.gw = gw;
+        P.m = d.n * gh * gw;
+        P.div_gw = make_fastdiv((uint32_t)gw);
+        P.div_ghw = make_fastdiv((uint32_t)(gh * gw));
+        P.doff_h = pa;
+        P.doff_w = pb;
+        for (int t = 0; t < T.count; ++t)
+          P.off[t] = (int32_t)((uint32_t)(uint16_t)(int16_t)offh[f][t] | ((uint32_t)offw[f][t] << 16));
+        // the OHWI weights read in place: taps in rows of equal r (the same grid as the
+        // gather offsets), byte steps between them
+        P.wostep = (int32_t)((int64_t)d.kh * d.kw * wpix2);
+        if (T.count > 0) {
+          int tw = 1;
+          while (tw < T.count && T.r[tw] == T.r[0]) ++tw;
+          P.wtoff0 = (int32_t)((T.r[0] * d.kw + T.s[0]) * wpix2);
+          P.wcstep = tw > 1 ? (int32_t)((T.s[1] - T.s[0]) * wpix2) : 0;
+          P.wrstep = T.count > tw
+                         ? (int32_t)(((T.r[tw] - T.r[tw - 1]) * d.kw + (T.s[tw] - T.s[tw - 1])) * wpix2)
+                         : 0;
+        }
+        mmax = P.m > mmax ? P.m : mmax;
+        ktmax = P.ktot > ktmax ? P.ktot : ktmax;
+      }
+      if (g.nphase > 0 && (g.nphase == kMaxPhases || last)) {
+        out->groups[out->ngroups] = g;
+        out->mmax[out->ngroups] = mmax;
+        out->ktmax[out->ngroups] = ktmax;
+        ++out->ngroups;
+        g.nphase = 0;
+        mmax = 0;
+        ktmax = 0;
+      }
+    }
+}
+
+// The reduction-splitting kernel's tile, where it is the one to run.  It has no other kernel to
+// fall back on, so it is chosen only where its own launch takes the problem's addresses.
 TileCfg split_tile(const ConvDesc& d, bool dgrad) {
   const TileCfg none{0, 0, -1, kVariantGeneric};
-  if (narrow(d)) return none;
-  constexpr int64_t kSpan = (1ll << 31) - (1ll << 25);
-  if ((int64_t)d.co * d.kh * d.kw * d.ci * 2 >= kSpan) return none;
+  if (narrow(d) || (int64_t)d.co * d.kh * d.kw * d.ci * 2 >= (1ll << 31) - (1ll << 25)) return none;
   if (!dgrad) {
-    if (((int64_t)d.n * d.h * d.w + 8ll * d.w) * d.x_pix * 2 >= kSpan) return none;
-    return convsplit_pick(d.m, d.co, d.ci, d.kh * d.kw * d.ci, 1, false);
+    const TileCfg t = convsplit_pick(d.m, d.co, d.ci, d.kh * d.kw * d.ci, 1, false);
+    return t.variant == kVariantSplit && convgemm_direct(fwd_geometry(d), t) ? t : none;
   }
-  if (((int64_t)d.n * d.ho * d.wo + 8ll * d.wo) * d.y_pix * 2 >= kSpan) return none;
   const int64_t mp = (int64_t)d.n * ((d.h + d.sh - 1) / d.sh) * ((d.w + d.sw - 1) / d.sw);
   const int tp = ((d.kh + d.sh - 1) / d.sh) * ((d.kw + d.sw - 1) / d.sw);
-  return convsplit_pick(mp, d.ci, d.co, tp * d.co, d.sh * d.sw, true);
+  const TileCfg t = convsplit_pick(mp, d.ci, d.co, tp * d.co, d.sh * d.sw, true);
+  if (t.variant != kVariantSplit) return none;
+  DgradGemms G;
+  dgrad_geometry(d, &G);
+  for (int i = 0; i < G.ngroups; ++i)
+    if (!convgemm_direct(G.groups[i], t)) return none;
+  return t;
 }
 
 size_t stats_bytes(const ConvDesc& d, int bm) {
@@ -429,26 +567,10 @@ numbat_status conv_fwd_launch(const ConvDesc& d, const void* x, const void* w, v
   hipError_t e;
   char* wsp = static_cast<char*>(ws);
   float2* part = batch_stats ? reinterpret_cast<float2*>(wsp) : nullptr;
-  const bf16_t* src = static_cast<const bf16_t*>(x);
-  const bf16_t* wt = static_cast<const bf16_t*>(w);
-  const int64_t src_pix = d.x_pix;
-  const int cs = d.ci;
-  ConvGemmArgs g;
-  std::memset(&g, 0, sizeof g);
-  g.src = src;
-  g.src_pix = src_pix;
-  g.hs = d.h;
-  g.ws = d.w;
-  g.cs = cs;
-  g.nout = d.co;
-  g.nimg = d.n;
-  g.gstride_h = d.sh;
-  g.gstride_w = d.sw;
+  ConvGemmArgs g = fwd_geometry(d);
+  g.src = static_cast<const bf16_t*>(x);
   g.dst = static_cast<bf16_t*>(y);
-  g.dst_pix = d.y_pix;
-  g.hd = d.ho;
-  g.wd = d.wo;
-  g.dstep_h = g.dstep_w = 1;
+  g.ph[0].wt = static_cast<const bf16_t*>(w);
   g.stats_part = part;
   g.post = post.kind;
   g.post_eps = post.eps;
@@ -465,19 +587,6 @@ numbat_status conv_fwd_launch(const ConvDesc& d, const void* x, const void* w, v
     g.pro_var = pro->var;
     g.pro_eps = pro->eps;
   }
-  g.nphase = 1;
-  GemmPhase& P = g.ph[0];
-  P.wt = wt;
-  P.taps = d.kh * d.kw;
-  P.ktot = P.taps * cs;
-  P.gh = d.ho;
-  P.gw = d.wo;
-  P.m = (int32_t)d.m;
-  P.div_gw = make_fastdiv((uint32_t)d.wo);
-  P.div_ghw = make_fastdiv((uint32_t)(d.ho * d.wo));
-  for (int r = 0; r < d.kh; ++r)
-    for (int q = 0; q < d.kw; ++q)
-      P.off[r * d.kw + q] = (int32_t)((uint32_t)(uint16_t)(int16_t)(r - d.ph) | ((uint32_t)(q - d.pw) << 16));
   if (t.variant == kVariantHalo)
     e = convhalo_launch(g, t, s, KC_CONV_FWD);
   else
@@ -792,123 +901,32 @@ static numbat_status conv_bwd_data_launch(const ConvDesc& d, const void* dy, con
     return ok();
   }
 
-  // stride phases (a, b): input rows h = a + sh*i read output rows p = i + (a + ph - r) / sh
-  const int cpad = d.ci;
-  PhaseTaps ph[16];
-  int first[16];
-  int nphase = 0, total = 0;
-  int offh[16][kMaxTaps], offw[16][kMaxTaps];
-  for (int pa = 0; pa < d.sh; ++pa)
-    for (int pb = 0; pb < d.sw; ++pb) {
-      PhaseTaps& f = ph[nphase];
-      f.count = 0;
-      for (int r = 0; r < d.kh; ++r) {
-        const int th = pa + d.ph - r;
-        if (((th % d.sh) + d.sh) % d.sh != 0) continue;
-        for (int s = 0; s < d.kw; ++s) {
-          const int tw = pb + d.pw - s;
-          if (((tw % d.sw) + d.sw) % d.sw != 0) continue;
-          f.r[f.count] = r;
-          f.s[f.count] = s;
-          offh[nphase][f.count] = (th - ((th % d.sh) + d.sh) % d.sh) / d.sh;  // exact
-          offw[nphase][f.count] = (tw - ((tw % d.sw) + d.sw) % d.sw) / d.sw;
-          ++f.count;
-        }
-      }
-      first[nphase] = total * cpad * d.co;
-      total += f.count;
-      ++nphase;
-    }
-  // all stride phases in launches of up to kMaxPhases phases (blockIdx.z = phase)
-  ConvGemmArgs g;
-  std::memset(&g, 0, sizeof g);
-  g.src = static_cast<const bf16_t*>(dy);
-  g.src_pix = d.y_pix;
-  g.hs = d.ho;
-  g.ws = d.wo;
-  g.cs = d.co;
-  g.nout = cpad;
-  g.nimg = d.n;
-  g.gstride_h = g.gstride_w = 1;
-  g.dst = static_cast<bf16_t*>(dx);
-  g.dst_pix = d.x_pix;
-  g.hd = d.h;
-  g.wd = d.w;
-  g.dstep_h = d.sh;
-  g.dstep_w = d.sw;
-  g.accumulate = accumulate ? 1 : 0;
-  ConvGemmArgs groups[16];
-  TileCfg tiles[16];
-  int ngroups = 0;
-  int f = 0;
-  int64_t mmax = 0;
-  int ktmax = 0;
-  const int64_t wpix2 = (int64_t)d.ci * 2;
-  for (int pa = 0; pa < d.sh; ++pa)
-    for (int pb = 0; pb < d.sw; ++pb, ++f) {
-      const int gh = pa < d.h ? (d.h - pa + d.sh - 1) / d.sh : 0;
-      const int gw = pb < d.w ? (d.w - pb + d.sw - 1) / d.sw : 0;
-      const bool last = (pa == d.sh - 1 && pb == d.sw - 1);
-      if (gh > 0 && gw > 0) {
-        GemmPhase& P = g.ph[g.nphase++];
-        const PhaseTaps& T = ph[f];
-        P.wt = static_cast<const bf16_t*>(ws) + first[f];  // re-laid-out copy (K-major)
-        P.taps = T.count;
-        P.ktot = P.taps * d.co;
-        P.gh = gh;
-        P.gw = gw;
-        P.m = d.n * gh * gw;
-        P.div_gw = make_fastdiv((uint32_t)gw);
-        P.div_ghw = make_fastdiv((uint32_t)(gh * gw));
-        P.doff_h = pa;
-        P.doff_w = pb;
-        for (int t = 0; t < T.count; ++t)
-          P.off[t] = (int32_t)((uint32_t)(uint16_t)(int16_t)offh[f][t] | ((uint32_t)offw[f][t] << 16));
-        // the OHWI weights read in place: taps in rows of equal r (the same grid as the
-        // gather offsets), byte steps between them
-        P.wostep = (int32_t)((int64_t)d.kh * d.kw * wpix2);
-        if (T.count > 0) {
-          int tw = 1;
-          while (tw < T.count && T.r[tw] == T.r[0]) ++tw;
-          P.wtoff0 = (int32_t)((T.r[0] * d.kw + T.s[0]) * wpix2);
-          P.wcstep = tw > 1 ? (int32_t)((T.s[1] - T.s[0]) * wpix2) : 0;
-          P.wrstep = T.count > tw
-                         ? (int32_t)(((T.r[tw] - T.r[tw - 1]) * d.kw + (T.s[tw] - T.s[tw - 1])) * wpix2)
-                         : 0;
-        }
-        mmax = P.m > mmax ? P.m : mmax;
-        ktmax = P.ktot > ktmax ? P.ktot : ktmax;
-      }
-      if (g.nphase > 0 && (g.nphase == kMaxPhases || last)) {
-        groups[ngroups] = g;
-        tiles[ngroups] = sp.variant == kVariantSplit ? sp : convgemm_pick(mmax, cpad, d.co, ktmax, g.nphase, true);
-        ++ngroups;
-        g.nphase = 0;
-        mmax = 0;
-        ktmax = 0;
-      }
-    }
+  DgradGemms G;
+  dgrad_geometry(d, &G);
+  TileCfg tiles[4];
+  for (int i = 0; i < G.ngroups; ++i) {
+    ConvGemmArgs& g = G.groups[i];
+    g.src = static_cast<const bf16_t*>(dy);
+    g.dst = static_cast<bf16_t*>(dx);
+    g.accumulate = accumulate ? 1 : 0;
+    tiles[i] = sp.variant == kVariantSplit ? sp : convgemm_pick(G.mmax[i], d.ci, d.co, G.ktmax[i], g.nphase, true);
+  }
   // the direct-to-LDS kernel reads the weights in place; any other kernel takes them
   // re-laid out per phase (K-major) in the workspace
-  bool direct = (int64_t)d.co * d.kh * d.kw * wpix2 < (int64_t)1 << 31;
-  for (int i = 0; i < ngroups && direct; ++i) {
-    ConvGemmArgs c = groups[i];
-    c.bt = 1;
-    for (int q = 0; q < c.nphase; ++q) c.ph[q].wt = static_cast<const bf16_t*>(w);
-    direct = convgemm_direct(c, tiles[i]);
-  }
-  if (direct) {
-    for (int i = 0; i < ngroups; ++i) {
-      groups[i].bt = 1;
-      for (int q = 0; q < groups[i].nphase; ++q) groups[i].ph[q].wt = static_cast<const bf16_t*>(w);
-    }
-  } else {
-    bf16_t* wt = static_cast<bf16_t*>(ws);
-    e = dgrad_weights_launch(static_cast<const bf16_t*>(w), wt, d.co, d.kh, d.kw, d.ci, cpad, first, ph, nphase, s);
+  bool direct = (int64_t)d.co * d.kh * d.kw * d.ci * 2 < (int64_t)1 << 31;
+  for (int i = 0; i < G.ngroups && direct; ++i) direct = convgemm_direct(G.groups[i], tiles[i]);
+  if (!direct) {
+    if (ws == nullptr) return fail(NUMBAT_ERR_WORKSPACE, "the data gradient re-lays this problem's weights out in a workspace");
+    e = dgrad_weights_launch(static_cast<const bf16_t*>(w), static_cast<bf16_t*>(ws), d.co, d.kh, d.kw, d.ci, d.ci,
+                             G.first, G.ph, G.nphase, s);
     if (e != hipSuccess) return hip_fail(e, "data-gradient weight re-layout launch");
   }
-  for (int i = 0; i < ngroups; ++i) {
-    e = convgemm_launch(groups[i], tiles[i], s, KC_CONV_DGRAD);
+  for (int i = 0; i < G.ngroups; ++i) {
+    ConvGemmArgs& g = G.groups[i];
+    g.bt = direct ? 1 : 0;
+    for (int q = 0; q < g.nphase; ++q)
+      g.ph[q].wt = direct ? static_cast<const bf16_t*>(w) : static_cast<const bf16_t*>(ws) + G.first[G.of[i][q]];
+    e = convgemm_launch(g, tiles[i], s, KC_CONV_DGRAD);
     if (e != hipSuccess) return hip_fail(e, "data-gradient launch");
   }
   return ok();

@@ -5,8 +5,7 @@
 // steps of 64 consecutive pixels, no halo, chunks of up to 288 input channels).
 //
 // A block owns one tile of output channels (64 or 96 rows) by one chunk of input channels
-// (32, or 48 for inputs whose channel count is a multiple of 48 but not of 32) across all
-// nine taps, and walks a contiguous range of PR x PC pixel patches of one image each.  Per
+// (32, or 48 where that pads the channels less) across all nine taps, and walks a contiguous range of PR x PC pixel patches of one image each.  Per
 // patch it stages in LDS, once, the patch's dy pixels and the (PR + 2) x (PC + 2) input
 // pixels that the nine taps reach (zeros outside the image), and reads every tap's MFMA
 // operand out of that halo with transposing LDS reads at the tap's pixel shift.  The
@@ -46,6 +45,14 @@ __device__ __forceinline__ void static_for(F&& f) {
   if constexpr (I < N) {
     f(IcH<I>{});
     static_for<I + 1, N>(f);
+  }
+}
+// the same until f returns false
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_while(F&& f) {
+  if constexpr (I < N) {
+    if (!f(IcH<I>{})) return;
+    static_while<I + 1, N>(f);
   }
 }
 
@@ -101,7 +108,11 @@ struct WhShape {
   static_assert(PENDING <= 63, "load counter");
 };
 
-template <int OB, int CK, int PR, int PC, int S, int KH>
+// RAG: patches pass the image's last row, on a boundary of their slices.  The slices past it
+// are left out and not multiplied by the zeros that dy reads there: the input pixels they pair
+// with at the tap row above are the image's own last row, and zero times an infinity or a NaN
+// is a NaN in a gradient that has no such product.
+template <int OB, int CK, int PR, int PC, int S, int KH, bool RAG>
 __global__ __launch_bounds__(512) void wgrad_halo_kernel(WgradArgs a, WhGeom g) {
   using Sh = WhShape<OB, CK, PR, PC, S, KH>;
   constexpr int KS = Sh::KS, RB = Sh::RB, HRB = Sh::HRB, HW = Sh::HW, R = Sh::R, NCB = Sh::NCB;
@@ -138,7 +149,7 @@ __global__ __launch_bounds__(512) void wgrad_halo_kernel(WgradArgs a, WhGeom g) 
   // This lane's part of load slot u of its wave (instruction n = wave + 8 u of a stage):
   // the byte offset of its 16 bytes from the step's base (kOobH: zeros) and the position of
   // its pixel: (row + 1) | (column + 1) << 16 relative to the patch origin (a patch may pass
-  // the image's last row or column: dy and input pixels there read zeros); in the 1x1 form
+  // the image's last row: dy and input pixels there read zeros); in the 1x1 form
   // the pixel's index within the step (the last step may pass the last pixel).
   uint32_t loff[LW];
   uint32_t lpos[LW];
@@ -268,7 +279,8 @@ __global__ __launch_bounds__(512) void wgrad_halo_kernel(WgradArgs a, WhGeom g) 
   // registers it does not have)
   // `after_first` runs once the first slice's fragment reads are issued (the next stage's
   // load issue then overlaps their latency)
-  auto compute = [&](auto sc, auto phc, auto parc, auto&& after_first) __attribute__((always_inline)) {
+  // (RAG: of the first `slices` slices)
+  auto compute = [&](auto sc, auto phc, auto parc, int slices, auto&& after_first) __attribute__((always_inline)) {
     constexpr int PH = decltype(phc)::value, PAR = decltype(parc)::value;
     constexpr int NK = (KS - PAR + 1) / 2;
     const unsigned char* Sg = stage(sc);
@@ -303,8 +315,10 @@ __global__ __launch_bounds__(512) void wgrad_halo_kernel(WgradArgs a, WhGeom g) 
     load(PAR, af0, bf0);
     __builtin_amdgcn_sched_barrier(0);
     after_first();
-    static_for<0, NK>([&](auto ic) {
+    // (a slice past the image ends the patch by a side exit: the others run as one straight line)
+    static_while<0, NK>([&](auto ic) __attribute__((always_inline)) -> bool {
       constexpr int i = decltype(ic)::value;
+      if (RAG && PAR + 2 * i >= slices) return false;  // (uniform)
       if constexpr ((i & 1) == 0) {
         if constexpr (i + 1 < NK) load(PAR + 2 * (i + 1), af1, bf1);
         mma(af0, bf0);
@@ -313,6 +327,7 @@ __global__ __launch_bounds__(512) void wgrad_halo_kernel(WgradArgs a, WhGeom g) 
         mma(af1, bf1);
       }
       __builtin_amdgcn_sched_barrier(0);
+      return true;
     });
   };
   auto sync = [&]() __attribute__((always_inline)) {
@@ -326,7 +341,13 @@ __global__ __launch_bounds__(512) void wgrad_halo_kernel(WgradArgs a, WhGeom g) 
     auto step = [&](auto uc, int kt) __attribute__((always_inline)) {
       constexpr int u = decltype(uc)::value;
       sync();
-      compute(uc, phc, parc, [&]() __attribute__((always_inline)) { issue(IcH<(u + S - 1) % S>{}, kt + S - 1); });
+      int slices = KS;
+      if constexpr (RAG) {
+        const uint32_t P = (uint32_t)(pbeg + kt), rem = P - fdiv(P, g.dppi) * (uint32_t)g.ppi;
+        slices = (a.h - (int)fdiv(rem, g.dpcols) * PR) * PC / 16;
+      }
+      compute(uc, phc, parc, slices,
+              [&]() __attribute__((always_inline)) { issue(IcH<(u + S - 1) % S>{}, kt + S - 1); });
     };
     static_for<0, S - 1>([&](auto ic) { issue(ic, decltype(ic)::value); });
     int kb = 0;
@@ -422,7 +443,7 @@ int wh_ob(int co) {
 // one to run: it executes at most kPadMost times the products of the general kernel, whose
 // tiles pad kh kw c_in to 128 columns.  It reads each input element about 1.4 times where the
 // general kernel gathers it per tap: 8 x 52 x 52, 192 -> 80 on 20 x 4 patches, 15% of them outside
-// the image, 27.3 -> 22.3 us; 5 x 45 x 48 x 256 29.8 -> 28.8.
+// the image, 27.9 -> 25.1 us; 5 x 45 x 48 x 256 30.4 -> 29.7.
 constexpr double kPadMost = 1.15;
 bool wh_cheaper(const WgradArgs& a, const WhCfg& c, int64_t pixels) {
   auto up = [](int64_t v, int64_t q) { return (v + q - 1) / q * q; };
@@ -469,18 +490,21 @@ WhCfg wgrad_halo_cfg(const WgradArgs& a) {
   // offsets within one image (plus its halo) are 32-bit
   const int64_t pix = a.x_pix > a.dy_pix ? a.x_pix : a.dy_pix;
   if (((int64_t)a.h * a.w + 2 * (int64_t)a.w + 2) * pix * 2 >= (1ll << 31) - (1ll << 24)) return c;
-  // the chunk that pads c_in least (32 on a tie), the patch that pads the image least (the
-  // first on a tie)
+  // the chunk that pads c_in least (32 on a tie); of the patches whose columns divide the image
+  // and whose slices of 16 pixels end with it (the kernel multiplies whole slices), the one that
+  // pads the image least (the first on a tie)
   const int pad32 = (a.ci + 31) / 32 * 32, pad48 = (a.ci + 47) / 48 * 48;
   c.ck = pad48 < pad32 ? 48 : 32;
-  c.ob = c.ck == 32 ? wh_ob(a.co) : 2;
   c.kh = 3;
   int64_t area = 0;
   constexpr int kPatch[3][2] = {{8, 16}, {20, 8}, {20, 4}};
   for (const auto& p : kPatch) {
-    const int64_t ar = (int64_t)((a.h + p[0] - 1) / p[0]) * p[0] * ((a.w + p[1] - 1) / p[1]) * p[1];
+    if (a.w % p[1] != 0 || a.h % p[0] * p[1] % 16 != 0) continue;
+    const int64_t ar = (int64_t)((a.h + p[0] - 1) / p[0]) * p[0] * a.w;
     if (area == 0 || ar < area) area = ar, c.pr = p[0], c.pc = p[1];
   }
+  if (area == 0) return c;
+  c.ob = c.ck == 32 ? wh_ob(a.co) : 2;
   const bool whole = area == (int64_t)a.h * a.w && (pad32 == a.ci || pad48 == a.ci);
   return whole || wh_cheaper(a, c, area * a.n) ? c : WhCfg{0, 0, 0, 0, 0};
 }
@@ -491,7 +515,13 @@ int64_t wh_npatch(const WgradArgs& a, const WhCfg& c) {
 
 template <int OB, int CK, int PR, int PC, int S, int KH>
 hipError_t launch_wh(const WgradArgs& a, const WhGeom& g, dim3 grid, hipStream_t s) {
-  NUMBAT_LAUNCH((wgrad_halo_kernel<OB, CK, PR, PC, S, KH>), grid, dim3(512), 0, s, a, g);
+  if constexpr (KH == 3) {
+    if (a.h % PR != 0) {
+      NUMBAT_LAUNCH((wgrad_halo_kernel<OB, CK, PR, PC, S, KH, true>), grid, dim3(512), 0, s, a, g);
+      return hipGetLastError();
+    }
+  }
+  NUMBAT_LAUNCH((wgrad_halo_kernel<OB, CK, PR, PC, S, KH, false>), grid, dim3(512), 0, s, a, g);
   return hipGetLastError();
 }
 

@@ -187,3 +187,37 @@ def test_forward_prologue_equals_the_two_calls(shape):
     torch.cuda.synchronize()
     assert torch.equal(y[0].view(torch.int16), y[1].view(torch.int16))
     assert torch.equal(st[0].view(torch.int32), st[1].view(torch.int32))
+
+
+# patches that pass the image's last row: 20 x 4, 8 x 16 (96-row tiles and a chunk that ends early;
+# 48-channel chunks; all but one row outside), 20 x 8; sizes whose patches' slices would pass it,
+# and the last column, on the general kernel
+@pytest.mark.parametrize("shape", [(2, 52, 52, 64, 80), (2, 45, 48, 88, 96), (3, 22, 32, 144, 40), (5, 41, 16, 32, 64),
+                                   (2, 30, 40, 32, 64), (2, 31, 45, 88, 72), (3, 18, 31, 144, 40), (9, 19, 7, 32, 64)])
+def test_weight_gradient_keeps_infinities_to_their_taps(shape):
+    """An infinity in the input's last row and a NaN in its last column reach the gradients of the
+    taps that pair them with an output pixel, and no other."""
+    n, h, w, ci, co = shape
+    s = ConvShape(n, h, w, ci, co, 3, 3, 1, 1, 1, 1)
+    ip = Inputs(145, ci)
+    xb, dyb = ip.normal(s.x_shape, synth.T_X), ip.normal(s.y_shape, synth.T_DY)
+    xb[0, h - 1, w // 2, 1], xb[n - 1, h // 2, w - 1, 9], xb[n - 1, h - 1, w - 1, ci - 1] = 0x7f80, 0x7fc0, 0xff80
+    blk = blocks.ConvBlock(n, h, w, ci, co, 3, 1)
+    dw = torch.empty(s.w_shape, device="cuda")
+    nb.numbat_conv_bwd_weight(blk.prob, blocks.dev_bf16(xb), blocks.dev_bf16(dyb), dw, False, blocks.workspace(blk.ws_bytes()))
+    torch.cuda.synchronize()
+    got = blocks.host_f64(dw)
+    # (the infinite input pixels' products by hand: the oracle's padding is not asked about them)
+    x64, dy64 = f64(xb), f64(dyb)
+    bad = ~np.isfinite(x64)
+    want = oracle.conv_wgrad(np.where(bad, 0.0, x64), dy64, s)
+    hit = np.zeros(s.w_shape, bool)
+    for img, i, j, c in np.argwhere(bad):
+        for r in range(3):
+            for q in range(3):
+                if 0 <= i + 1 - r < h and 0 <= j + 1 - q < w:
+                    hit[:, r, q, c] = True
+    assert hit.any() and not hit.all()
+    assert not np.isfinite(got[hit]).any()
+    assert np.isfinite(got[~hit]).all()
+    assert_close(np.where(hit, 0.0, got), np.where(hit, 0.0, want), "dw", 1e-5)

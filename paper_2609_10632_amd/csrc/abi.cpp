@@ -999,7 +999,6 @@ numbat_status numbat_conv_bwd_data_bn_silu_prologue(const numbat_conv_problem* p
   a.pro_y = static_cast<const bf16_t*>(y);
   a.pro_y_pix = d.y_pix;
   a.pro_dy = static_cast<bf16_t*>(dy);
-  a.pro_dy_pix = d.y_pix;
   a.pro_m = d.m;
   const hipError_t e = convhalo_launch(a, bwd_prologue_tile(d), static_cast<hipStream_t>(stream), KC_CONV_DGRAD);
   if (e != hipSuccess) return hip_fail(e, "data-gradient launch");

@@ -55,6 +55,15 @@ struct HaloShape {
   static_assert(TC == 0 || (G::BM % TC == 0 && (TR + 2) * (TC + 2) <= HPAD), "2D tile and its halo");
 };
 
+// Waves per SIMD the register allocation is held to.  The prologues on two-dimensional tiles of
+// two reduction halves need the two blocks per CU that their LDS allows; left to itself the
+// compiler took 129 registers for the forward (128 fit twice) and 269 for the backward (256 fit
+// twice): 16 x 160 x 160 x 48, forward 81.1 us with one block per CU and 57.2 with two, backward
+// 96.0 and 68.6 (on the four-wave kernel with one accumulator set: 62.0 and 67.1).
+constexpr int halo_min_waves(int tc, int pro, int kv, int kp) {
+  return tc > 0 && pro != kProNone && kp == 2 ? 2 * kv : 1;
+}
+
 // KV = 2: eight waves in two halves of four; half 0 issues every load, half k multiplies
 // reduction slice k (16 channels) of every tap, and the halves add their sums through LDS
 // before the epilogue (twice the waves per SIMD to cover a step's latencies, same LDS).  On
@@ -66,16 +75,21 @@ struct HaloShape {
 //
 // PRO (kProFwd, kProBwd): an element-wise prologue on each 32-channel chunk of the staged
 // halo, once per element, before any tap reads it; its per-channel constants sit in dynamic
-// LDS (2 or 4 floats per source channel, sized at launch), and the loading lanes transform
-// their own chunks between their load wait and the barrier.  kProBwd (the data gradient,
+// LDS (2 or 4 floats per source channel, sized at launch), and the loading lanes (of a
+// forward's two halves, both on linear tiles) transform their chunks between their load wait and the barrier.  kProBwd (the data gradient,
 // four waves): the halo holds g, each lane also loads y for its own halo chunks (into
 // registers, a chunk ahead), and dy = BN + SiLU backward (g, y) replaces g in place; dy of
 // the tile's own pixels is also stored (first column tile only).
 template <int TM, int TN, int HI, int KT, int SB, bool BT, int TC, int PRO, int KV, int KP, bool TL>
-__global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
+__global__ __launch_bounds__(256 * KV, halo_min_waves(TC, PRO, KV, KP)) void convhalo_kernel(ConvGemmArgs a) {
   using G = GemmShape<TM, TN, 4>;
   using Sh = HaloShape<TM, TN, HI, KT, SB, BT, TC, KP>;
   constexpr bool XROWS = KV == 2 && TM == 2;  // the halves share out the rows of the epilogue
+  // On linear tiles both halves transform the forward prologue's halo, at a barrier more per
+  // chunk (16 x 40 x 40 x 192, 256-row tiles: 35.6 -> 30.7 us, 16 x 20 x 20 x 288, 128-row ones: 30.7 ->
+  // 27.9); two-dimensional tiles overlap half 0's transform with their CU's other block (32 x
+  // 160 x 160, 32 -> 64: 76.4 us with both halves, 73.2 with half 0).
+  constexpr bool PSHARE = PRO == kProFwd && KV == 2 && TC == 0;
   constexpr int TR = Sh::TR;
   constexpr int BM = G::BM, BN = G::BN, WTM = G::WTM, NW = 4, SPC = Sh::SPC, D = SB - 1;
   constexpr int BI = Sh::BI, BI_MIN = Sh::BI_MIN, BI_MAX = Sh::BI_MAX, TBYTES = Sh::TBYTES;
@@ -166,35 +180,32 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
       TC > 0 ? ((int64_t)img2 * H + h0 - 1) * W + w0 - 1 : (int64_t)m0 - W - 1;
   const __amdgpu_buffer_rsrc_t rsA = buffer_rsrc(a.src + hbase_px * a.src_pix);
   uint32_t hoff[HI];
-  int hc8[HI];  // channel of the lane's chunk within a 32-channel chunk
+  // channel of the lane's chunk within a 32-channel chunk, the same for every instruction
+  const int hc8 = 8 * ((lane & 3) ^ ((lane >> 4) & 3));
 #pragma unroll
   for (int q = 0; q < HI; ++q) {
     const int j = (q * NW + wave) * 16 + (lane >> 2);
-    const int lc = (lane & 3) ^ ((j >> 2) & 3);
     if constexpr (TC > 0) {
       const int hr = j / (TC + 2), hcol = j - hr * (TC + 2);
       const bool ok = j < (TR + 2) * (TC + 2) && (unsigned)(h0 - 1 + hr) < (unsigned)H &&
                       (unsigned)(w0 - 1 + hcol) < (unsigned)W;
-      hoff[q] = ok ? (uint32_t)(((int64_t)hr * W + hcol) * pix2 + lc * 16) : kOob;
-      hc8[q] = ok ? lc * 8 : (1 << 20);
+      hoff[q] = ok ? (uint32_t)(((int64_t)hr * W + hcol) * pix2 + hc8 * 2) : kOob;
     } else {
       const int64_t src_px = hbase_px + j;
       const bool ok = src_px >= 0 && src_px < npix && j < BM + 2 * W + 2;
-      hoff[q] = ok ? (uint32_t)(j * pix2 + lc * 16) : kOob;
-      hc8[q] = ok ? lc * 8 : (1 << 20);
+      hoff[q] = ok ? (uint32_t)(j * pix2 + hc8 * 2) : kOob;
     }
   }
-  // backward prologue: byte offset of the lane's chunk of halo instruction q in a tensor of
-  // pixel stride pix (relative to that tensor's halo base pixel; valid where hoff[q] is),
+  // backward prologue: byte offset of the lane's chunk of halo instruction q in y and dy (one
+  // pixel stride; relative to the tensor's halo base pixel; valid where hoff[q] is),
   // and whether its pixel is one of the tile's own output pixels (the halo's interior)
-  auto chunk_off = [&](int q, int64_t pix) __attribute__((always_inline)) -> uint32_t {
+  auto chunk_off = [&](int q) __attribute__((always_inline)) -> uint32_t {
     const int j = (q * NW + wave) * 16 + (lane >> 2);
-    const int lc = (lane & 3) ^ ((j >> 2) & 3);
     if constexpr (TC > 0) {
       const int hr = j / (TC + 2), hcol = j - hr * (TC + 2);
-      return (uint32_t)(((int64_t)hr * W + hcol) * pix * 2 + lc * 16);
+      return (uint32_t)(((int64_t)hr * W + hcol) * a.pro_y_pix * 2 + hc8 * 2);
     } else {
-      return (uint32_t)(j * pix * 2 + lc * 16);
+      return (uint32_t)(j * a.pro_y_pix * 2 + hc8 * 2);
     }
   };
   auto interior = [&](int q) __attribute__((always_inline)) -> bool {
@@ -207,7 +218,7 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
     }
   };
   const __amdgpu_buffer_rsrc_t rsY = buffer_rsrc(PRO == kProBwd ? a.pro_y + hbase_px * a.pro_y_pix : a.src);
-  const __amdgpu_buffer_rsrc_t rsD = buffer_rsrc(PRO == kProBwd ? a.pro_dy + hbase_px * a.pro_dy_pix : a.dst);
+  const __amdgpu_buffer_rsrc_t rsD = buffer_rsrc(PRO == kProBwd ? a.pro_dy + hbase_px * a.pro_y_pix : a.dst);
   u32x4 yv[PRO == kProBwd ? HI : 1];  // y of the lane's chunks of the next chunk to transform
 
   // ---- weight loads: instruction u of a step covers 1 KiB of tap u / (BI / KT)'s stage
@@ -248,7 +259,7 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
     const int cb = 32 * c;
 #pragma unroll
     for (int q = 0; q < HI; ++q) {
-      const uint32_t v = cb + hc8[q] < cs ? hoff[q] : kOob;
+      const uint32_t v = cb + hc8 < cs ? hoff[q] : kOob;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void_t*)(Hb + (q * NW + wave) * 1024), 16, v,
                                                (uint32_t)(cb * 2), 0, 0);
     }
@@ -403,7 +414,7 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
       const int cb = 32 * c;
 #pragma unroll
       for (int q = 0; q < HI; ++q) {
-        const uint32_t v = (hoff[q] != kOob && cb + hc8[q] < cs) ? chunk_off(q, a.pro_y_pix) : kOob;
+        const uint32_t v = (hoff[q] != kOob && cb + hc8 < cs) ? chunk_off(q) : kOob;
         yv[q] = __builtin_amdgcn_raw_buffer_load_b128(rsY, v, (uint32_t)(cb * 2), 0);
       }
     }
@@ -419,8 +430,7 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
   auto transform_bwd = [&](auto hc, int c) __attribute__((always_inline)) {
     unsigned char* Hb = hbuf(hc);
     const int cb = 32 * c;
-    const int c8 = 8 * ((lane & 3) ^ ((lane >> 4) & 3));
-    const int ch = cb + c8 < cs ? cb + c8 : 0;
+    const int ch = cb + hc8 < cs ? cb + hc8 : 0;
 #pragma unroll
     for (int ps = 0; ps < 2; ++ps) {
       float ka[4], kb[4], kc[4], kd[4];
@@ -433,7 +443,7 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
       }
 #pragma unroll
       for (int q = 0; q < HI; ++q) {
-        const bool live = hoff[q] != kOob && cb + hc8[q] < cs;
+        const bool live = hoff[q] != kOob && cb + hc8 < cs;
         unsigned char* p = Hb + (q * NW + wave) * 1024 + lane * 16;
         // pass 0: the first 4 channels; pass 1: the last 4, with the first 4 as pass 0 left them
         u32x4 v;
@@ -452,7 +462,7 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
         const uint2 oh = make_uint2(pack2(o0, o1), pack2(o2, o3));
         if (live) *reinterpret_cast<uint2*>(p + 8 * ps) = oh;
         if (ps == 1) {
-          const uint32_t so = (live && T.nt == 0 && interior(q)) ? chunk_off(q, a.pro_dy_pix) : kOob;
+          const uint32_t so = (live && T.nt == 0 && interior(q)) ? chunk_off(q) : kOob;
           __builtin_amdgcn_raw_buffer_store_b128(u32x4{v[0], v[1], oh.x, oh.y}, rsD, so, (uint32_t)(cb * 2), 0);
           // wait states before anything rewrites the store's data registers: with the
           // scheduling barrier right after it, the compiler issued a VALU write to the first
@@ -464,22 +474,22 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
       }
     }
   };
-  // prologue: this lane's own 16-byte chunks of chunk c's halo (landed: the wait before
+  // prologue: this lane's 16-byte chunks of chunk c's halo (landed: the wait before
   // this covers them) become the previous layer's activations, SiLU(BN(y)), in place;
   // chunks that loaded zeros (padding, past the image or the channels) stay zero
   auto transform = [&](auto hc, int c) __attribute__((always_inline)) {
     if constexpr (PRO != kProFwd) return;
-    if (KV == 2 && kh != 0) return;  // (the chunks are half 0's loads)
     unsigned char* Hb = hbuf(hc);
     const int cb = 32 * c;
 #pragma unroll
     for (int q = 0; q < HI; ++q) {
-      if (hoff[q] != kOob && cb + hc8[q] < cs) {
+      if (KV == 2 && (PSHARE ? (q & 1) != kh : kh != 0)) continue;  // (uniform)
+      if (hoff[q] != kOob && cb + hc8 < cs) {
         u32x4* p = reinterpret_cast<u32x4*>(Hb + (q * NW + wave) * 1024 + lane * 16);
         const u32x4 v = *p;
         float f[8];
         unpack8(uint4{v[0], v[1], v[2], v[3]}, f);
-        const int ch = cb + hc8[q];
+        const int ch = cb + hc8;
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] = bn_silu_apply(f[e], s_pro[ch + e], s_pro[cs + ch + e]);
         const uint4 o = pack8(f);
@@ -495,7 +505,9 @@ __global__ __launch_bounds__(256 * KV) void convhalo_kernel(ConvGemmArgs a) {
     constexpr int waitn = (D - 1) * BI_MIN + ((k >= 1 && k <= D - 1) ? XB : 0);
     if constexpr (PRO == kProFwd && k == 0) {
       // the chunk's halo has landed for this wave: transform this lane's part, then publish
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(waitn) : "memory");
+      // (they are half 0's loads: it publishes them before both halves transform)
+      if constexpr (PSHARE) sync(Ic<waitn>{});
+      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(waitn) : "memory");
       transform(hc, c);
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     } else if constexpr (PRO == kProBwd && k == 0) {

@@ -134,7 +134,7 @@ struct ConvGemmArgs {
   const float *pro_rstd, *pro_dgamma, *pro_dbeta;
   const bf16_t* pro_y;
   bf16_t* pro_dy;
-  int64_t pro_y_pix, pro_dy_pix, pro_m;
+  int64_t pro_y_pix, pro_m;
   GemmPhase ph[kMaxPhases];
 };
 enum { kProNone = 0, kProFwd = 1, kProBwd = 2 };

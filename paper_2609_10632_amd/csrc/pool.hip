@@ -3,7 +3,8 @@
 // with pixel strides (so inputs and outputs can be channel slices of concatenation
 // buffers).  A thread works on 16-byte vectors of 8 channels of one pixel.
 //
-// Max pool: a block takes a tile of kTileRows output rows by up to kTileCols columns of one
+// Max pool, where tiles are the better (pool_tiles; elsewhere a thread reads each of its vector's
+// 25 window positions from memory): a block takes a tile of kTileRows output rows by up to kTileCols columns of one
 // image for four vectors (64 bytes of every pixel) and stages the tile and its border of two
 // pixels in LDS, so an element is read from memory about twice and not 25 times.
 //  * Forward: the window's first maximum in row-major order wins (a later equal value does
@@ -211,6 +212,93 @@ __global__ __launch_bounds__(kTileThreads) void maxpool5_bwd_kernel(PoolArgs a, 
   }
 }
 
+// the max pools one output (or input) vector per thread, its window read from memory
+__global__ __launch_bounds__(kPoolThreads) void maxpool5_fwd_direct_kernel(PoolArgs a, const bf16_t* x, bf16_t* y,
+                                                                           uint8_t* idx) {
+  const int cv = a.c / 8;
+  const int64_t nvec = (int64_t)a.n * a.h * a.w * cv;
+  for (int64_t v = (int64_t)blockIdx.x * kPoolThreads + threadIdx.x; v < nvec; v += (int64_t)gridDim.x * kPoolThreads) {
+    const int64_t pix = v / cv;
+    const int ch = (int)(v - pix * cv) * 8;
+    const int64_t img = pix / ((int64_t)a.h * a.w);
+    const int rem = (int)(pix - img * a.h * a.w);
+    const int p = rem / a.w, q = rem - p * a.w;
+    float best[8];
+    uint32_t at[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      best[e] = -__builtin_huge_valf();
+      at[e] = 0;
+    }
+    for (int r = 0; r < 5; ++r) {
+      const int i = p + r - 2;
+      if ((unsigned)i >= (unsigned)a.h) continue;
+      for (int s = 0; s < 5; ++s) {
+        const int j = q + s - 2;
+        if ((unsigned)j >= (unsigned)a.w) continue;
+        float f[8];
+        unpack8(*reinterpret_cast<const uint4*>(x + ((img * a.h + i) * a.w + j) * a.x_pix + ch), f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const bool better = f[e] > best[e];
+          best[e] = better ? f[e] : best[e];
+          at[e] = better ? (uint32_t)(r * 5 + s) : at[e];
+        }
+      }
+    }
+    *reinterpret_cast<uint4*>(y + pix * a.y_pix + ch) = pack8(best);  // bf16 values: exact
+    if (idx != nullptr) {
+      uint2 b;
+      b.x = at[0] | (at[1] << 8) | (at[2] << 16) | (at[3] << 24);
+      b.y = at[4] | (at[5] << 8) | (at[6] << 16) | (at[7] << 24);
+      *reinterpret_cast<uint2*>(idx + pix * a.c + ch) = b;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kPoolThreads) void maxpool5_bwd_direct_kernel(PoolArgs a, const bf16_t* dy, const uint8_t* idx,
+                                                                           bf16_t* dx, int accumulate) {
+  const int cv = a.c / 8;
+  const int64_t nvec = (int64_t)a.n * a.h * a.w * cv;
+  for (int64_t v = (int64_t)blockIdx.x * kPoolThreads + threadIdx.x; v < nvec; v += (int64_t)gridDim.x * kPoolThreads) {
+    const int64_t pix = v / cv;
+    const int ch = (int)(v - pix * cv) * 8;
+    const int64_t img = pix / ((int64_t)a.h * a.w);
+    const int rem = (int)(pix - img * a.h * a.w);
+    const int i = rem / a.w, j = rem - i * a.w;
+    float acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+    // window of output (p, q) holds this pixel at position (r, s) = (i - p + 2, j - q + 2)
+    for (int r = 0; r < 5; ++r) {
+      const int p = i - r + 2;
+      if ((unsigned)p >= (unsigned)a.h) continue;
+      for (int s = 0; s < 5; ++s) {
+        const int q = j - s + 2;
+        if ((unsigned)q >= (unsigned)a.w) continue;
+        const int64_t op = (img * a.h + p) * a.w + q;
+        const uint2 b = *reinterpret_cast<const uint2*>(idx + op * a.c + ch);
+        float g[8];
+        unpack8(*reinterpret_cast<const uint4*>(dy + op * a.y_pix + ch), g);
+        const uint32_t pos = (uint32_t)(r * 5 + s);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const uint32_t w = ((e < 4 ? b.x : b.y) >> (8 * (e & 3))) & 0xffu;
+          acc[e] += w == pos ? g[e] : 0.f;
+        }
+      }
+    }
+    uint4* o = reinterpret_cast<uint4*>(dx + pix * a.x_pix + ch);
+    if (accumulate) {
+      float f[8];
+      unpack8(*o, f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += f[e];
+    }
+    *o = pack8(acc);
+  }
+}
+
 // vector index -> pixel and image row
 struct UpDiv {
   int32_t small;  // every index below 2^31
@@ -304,12 +392,24 @@ UpDiv up_div(const PoolArgs& a) {
   return d;
 }
 
-bool pool_tiles(const PoolArgs& a, PoolTiles* T) {
-  const int64_t nvec = (a.c / 8 + kTileVecs - 1) / kTileVecs;
+// Whether a max pool runs on tiles, and its tiles.  A tile leaves idle the lanes of missing
+// vectors (c = 8: three of four) and of columns past the image (41 wide: 23 of 64), walks at most
+// 512 threads twice over its vectors from 26 columns up, and has a border to stage; the direct
+// kernel reads a window's vectors from the caches.  Tiles against direct, us, forward / backward:
+// 8 images of 20 x 20 x 192 5.9 : 8.7 / 7.5 : 10.1, 32 of 64 x 64 x 192 69 : 95 / 92 : 123, but 32 of
+// 80 x 80 x 8 22.4 : 12.2 / 29.0 : 12.4, 41 x 41 x 192 46.6 : 43.1 / 59.9 : 55.1.  So tiles where at
+// least three quarters of their vectors exist (forward also up to 32 columns: 8 images of 26 x 26 x
+// 8 5.9 : 6.9), and backward past 20 columns from 600000 vectors up (40 x 40 x 288, one image 11.4 :
+// 9.7, 8 25.6 : 23.6, 32 58.2 : 77.3).  One column: 4.1 : 3.6 / 6.4 : 4.1.  A launch holds below 2^32
+// threads, which 2^22 tiles stay under; the direct kernel walks over any size.
+bool pool_tiles(const PoolArgs& a, bool backward, PoolTiles* T) {
+  const int64_t cv = a.c / 8, nvec = (cv + kTileVecs - 1) / kTileVecs;
   T->tw = a.w <= kWholeCols ? a.w : kTileCols;
   const int64_t ncol = (a.w + T->tw - 1) / T->tw, nband = (a.h + kTileRows - 1) / kTileRows;
   const int64_t count = nvec * ncol * nband * a.n;
-  if (count >= (1ll << 31)) return false;  // (over 10 TB of input)
+  const bool full = 4 * a.w * cv >= 3 * ncol * T->tw * nvec * kTileVecs;
+  const bool on = backward ? full && (a.w <= 20 || (int64_t)a.n * a.h * a.w * cv >= 600000) : full || a.w <= 32;
+  if (!on || a.w == 1 || count > (1ll << 22)) return false;
   T->count = (uint32_t)count;
   const int work = kTileRows * T->tw * kTileVecs;
   T->threads = work < kTileThreads ? (work + 63) / 64 * 64 : kTileThreads;
@@ -323,10 +423,13 @@ bool pool_tiles(const PoolArgs& a, PoolTiles* T) {
 
 hipError_t maxpool5_fwd_launch(const PoolArgs& a, const bf16_t* x, bf16_t* y, uint8_t* idx, hipStream_t s) {
   PoolTiles T;
-  if (!pool_tiles(a, &T)) return hipErrorInvalidValue;
-  const size_t smem = (size_t)(kTileRows + 4) * kTileVecs * ((T.tw + 4) * 16 + T.tw * 24);
   trace_begin(KC_POOL);
-  NUMBAT_LAUNCH(maxpool5_fwd_kernel, dim3(T.count), dim3(T.threads), smem, s, a, T, x, y, idx);
+  if (pool_tiles(a, false, &T)) {
+    const size_t smem = (size_t)(kTileRows + 4) * kTileVecs * ((T.tw + 4) * 16 + T.tw * 24);
+    NUMBAT_LAUNCH(maxpool5_fwd_kernel, dim3(T.count), dim3(T.threads), smem, s, a, T, x, y, idx);
+  } else {
+    NUMBAT_LAUNCH(maxpool5_fwd_direct_kernel, dim3(pool_blocks(a)), dim3(kPoolThreads), 0, s, a, x, y, idx);
+  }
   trace_end(KC_POOL);
   return hipGetLastError();
 }
@@ -334,10 +437,14 @@ hipError_t maxpool5_fwd_launch(const PoolArgs& a, const bf16_t* x, bf16_t* y, ui
 hipError_t maxpool5_bwd_launch(const PoolArgs& a, const bf16_t* dy, const uint8_t* idx, bf16_t* dx, int accumulate,
                                hipStream_t s) {
   PoolTiles T;
-  if (!pool_tiles(a, &T)) return hipErrorInvalidValue;
-  const size_t smem = (size_t)(kTileRows + 4) * kTileVecs * (T.tw + 4) * 24;
   trace_begin(KC_POOL);
-  NUMBAT_LAUNCH(maxpool5_bwd_kernel, dim3(T.count), dim3(T.threads), smem, s, a, T, dy, idx, dx, accumulate);
+  if (pool_tiles(a, true, &T)) {
+    const size_t smem = (size_t)(kTileRows + 4) * kTileVecs * (T.tw + 4) * 24;
+    NUMBAT_LAUNCH(maxpool5_bwd_kernel, dim3(T.count), dim3(T.threads), smem, s, a, T, dy, idx, dx, accumulate);
+  } else {
+    NUMBAT_LAUNCH(maxpool5_bwd_direct_kernel, dim3(pool_blocks(a)), dim3(kPoolThreads), 0, s, a, dy, idx, dx,
+                  accumulate);
+  }
   trace_end(KC_POOL);
   return hipGetLastError();
 }

@@ -292,10 +292,12 @@ __global__ __launch_bounds__(kFinCh * G) void bn_bwd_finalize_kernel(const float
 
 // The finalize inside the apply, for few partials: every block adds all of them by itself, so
 // a launch of its own (3.9 us for the emptiest kernel, as much as a small apply) goes away.
-// kFoldMax bounds nblocks * c: 16 partials a thread and 32 KiB a block, which the apply
-// blocks read from L2.  Finalize + apply -> apply: 2048 rows of 32 channels 8.2 -> 4.9 us, 2450
-// of 128 8.5 -> 6.9; with twice the partials the two launches are as fast.
-constexpr int kFoldMax = 4096;
+// A thread reads its partials of one channel one behind another, so they are worth the launch
+// up to kFoldMost a thread and for channels that one trip of the threads covers.  The whole
+// backward back to back against three launches, mean over random sizes by partials a thread: 1
+// 0.92, 4 0.97, 5 0.98, 7 1.02, 10 1.07, 14 1.12 (20 x 37 x 37 x 80 12.2 -> 13.7 us); past 256 channels
+// 1.09 from 2 on.
+constexpr int kFoldMost = 5;
 
 // this block's folded constants coef[4][c] in LDS from the reduce's partials (fp64 sums in a
 // fixed order: G thread groups per channel, each over nblocks / G partials G apart, then the
@@ -498,7 +500,7 @@ hipError_t bn_bwd_launch(const BnArgs& a, const bf16_t* g, const bf16_t* y, cons
   trace_end(KC_BN_BWD_REDUCE);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (dy != nullptr && (int64_t)nb * a.c <= kFoldMax) {
+  if (dy != nullptr && a.c <= kThreads && nb <= kFoldMost * (kThreads / a.c)) {
     int64_t rows = 0;
     const int ab = apply_blocks(a.m, a.c, &rows);
     trace_begin(KC_BN_BWD_APPLY);

@@ -118,9 +118,10 @@ def test_inference_outputs(i):
     assert_close(blocks.host_f64(y2), oracle.bn_silu_eval(yref, f(m), f(v), f(g), f(b), EPS), "conv + eval BN + SiLU")
 
 
-# rows, channels: at most 4096 partials (the apply adds them itself) and just past it; one
-# partial; more channels than threads
-@pytest.mark.parametrize("m,c", [(65536, 32), (65537, 32), (300, 8), (784, 288), (785, 288), (16, 2048), (50, 264)])
+# rows, channels: at most five partials a thread (the apply adds them itself) and just past
+# it; one partial; more channels than threads
+@pytest.mark.parametrize("m,c", [(65536, 32), (65537, 32), (300, 8), (784, 288), (785, 288), (16, 2048), (50, 264),
+                                 (20480, 32), (20481, 32), (320, 256), (321, 256), (500, 200)])
 def test_bn_backward_folds_few_partials(m, c):
     ip = Inputs(142, c)
     yb, gb = ip.normal((m, c), synth.T_Y, 0.3, 2.0), ip.normal((m, c), synth.T_G)

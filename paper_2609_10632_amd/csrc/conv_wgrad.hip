@@ -400,12 +400,7 @@ static int64_t wgrad_splits_for(int64_t tiles, int64_t steps) {
   if (const char* e = getenv("NUMBAT_WG_SLOTS")) slots = atoi(e);
 #endif
   int64_t splits = tiles < slots ? slots / tiles : 1;
-  // small pixel counts: down to 4 quanta per split while the grid has fewer than 256 blocks
-  // (2 x 32 x 32, 16 -> 32: 2 splits of 16 quanta 16.4 us, 8 of 4 8.3; 100 x 98, 88 -> 128 at
-  // stride 2: 19.2 -> 9.9)
-  const int64_t few = steps / 4 < 256 / tiles ? steps / 4 : 256 / tiles;
-  int64_t max_by_steps = steps / 16 > few ? steps / 16 : few;
-  if (max_by_steps < 1) max_by_steps = 1;
+  const int64_t max_by_steps = steps / 16 > 0 ? steps / 16 : 1;
   if (splits > max_by_steps) splits = max_by_steps;
   if (splits > 256) splits = 256;
   return splits < 1 ? 1 : splits;
@@ -452,6 +447,18 @@ int wgrad_pick_splits(int64_t m, int co, int ktot, int64_t* rows_per_split) {
   const int tiles = (int)(((co + bmo - 1) / bmo) * ((ktot + BNK - 1) / BNK));
   const int64_t steps = (m + kSplitQuantum - 1) / kSplitQuantum;
   int64_t splits = wgrad_splits_for(tiles, steps);
+  // Small pixel counts: down to 4 quanta per split while the grid has fewer than 256 blocks
+  // (2 x 32 x 32, 16 -> 32: 2 splits of 16 quanta 16.4 us, 8 of 4 8.3; 100 x 98, 88 -> 128 at stride
+  // 2: 19.2 -> 9.9), where the quanta saved (about 0.9 us each on such a grid) outweigh the
+  // partials (written and read at about 2.5 TB/s, and 4 us for a reduce that one split does
+  // without): 25 x 25, 352 -> 608, 2 splits of 5 quanta 21.7 us, one of 10 13.3; 9 x 15 x 15, 280 ->
+  // 600 at stride 2 19.5 and 12.4; 8 x 14 x 14, 592 -> 144, 2 of 12 19.7, one of 25 23.1.
+  const int64_t few = steps / 4 < 256 / tiles ? steps / 4 : 256 / tiles;
+  if (few > splits) {
+    const double saved = 0.9 * ((double)steps / splits - (double)steps / few);
+    const double more = (double)(splits > 1 ? few - splits : few) * co * ktot * 8 / 2.5e6 + (splits > 1 ? 0 : 4);
+    if (saved > more) splits = few;
+  }
   // partials at most 64 MiB
   const int64_t part_bytes = (int64_t)co * ktot * 4;
   while (splits > 1 && splits * part_bytes > (64ll << 20)) --splits;

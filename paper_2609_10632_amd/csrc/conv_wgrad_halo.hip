@@ -439,19 +439,54 @@ int wh_ob(int co) {
   return pad3 <= pad2 ? 3 : 2;
 }
 
+int64_t wh_npatch(const WgradArgs& a, const WhCfg& c) {
+  return c.kh == 1 ? (a.m + 63) / 64 : (int64_t)a.n * ((a.h + c.pr - 1) / c.pr) * ((a.w + c.pc - 1) / c.pc);
+}
+
+// Blocks: about 160.  One block fills a CU (all of its LDS and registers), and the
+// weight gradients run beside the backward's main chain on a second stream: grids that
+// leave that chain CUs made the two-stream step faster though the kernel alone is slower
+// (configuration 4 at batch 16: 256 blocks 8.91 ms per step, 192 8.73, 160 8.54, 128
+// 8.57, against 8.75 with the general kernel on every layer, same host); fewer blocks
+// also write fewer partials.
+constexpr int64_t kWhSlots = 160;
+int64_t wh_tiles(const WgradArgs& a, const WhCfg& c) {
+  return (int64_t)((a.co + 32 * c.ob - 1) / (32 * c.ob)) * ((a.ci + c.ck - 1) / c.ck);
+}
+int64_t wh_splits(const WgradArgs& a, const WhCfg& c) {
+  int64_t slots = kWhSlots;
+#ifdef NUMBAT_TUNING
+  if (const char* e = getenv("NUMBAT_WH_SLOTS")) slots = atoi(e);
+#endif
+  const int64_t tiles = wh_tiles(a, c), npatch = wh_npatch(a, c);
+  int64_t sp = tiles < slots ? slots / tiles : 1;
+  if (sp > npatch) sp = npatch;
+  // partials at most 64 MiB
+  const int64_t part_bytes = (int64_t)a.co * c.kh * c.kh * a.ci * 4;
+  while (sp > 1 && sp * part_bytes > (64ll << 20)) --sp;
+  return sp;
+}
+
 // Whether a configuration that pads channels or pixels (`pixels` staged in all) is still the
 // one to run: it executes at most kPadMost times the products of the general kernel, whose
-// tiles pad kh kw c_in to 128 columns.  It reads each input element about 1.4 times where the
-// general kernel gathers it per tap: 8 x 52 x 52, 192 -> 80 on 20 x 4 patches, 15% of them outside
-// the image, 27.9 -> 25.1 us; 5 x 45 x 48 x 256 30.4 -> 29.7.
+// tiles pad kh kw c_in to 128 columns; where patches pass the image, in several chunks (one, 2 x 76 x
+// 76, 48 -> 288: 23.0 -> 25.7 us) and on a grid that fills its block slots (the general kernel's grid always comes near its own).  It reads each input element
+// about 1.4 times where the general kernel gathers it per tap: 8 x 52 x 52, 192 -> 80 on 20 x 4
+// patches, 15% of them outside the image, 27.9 -> 25.1 us; 5 x 45 x 48 x 256 30.4 -> 29.7; but 7 x 242
+// x 8, 704 -> 216 in 88 blocks 75 -> 115, 8 x 92 x 92, 576 -> 336 in 144 387 -> 412.
 constexpr double kPadMost = 1.15;
-bool wh_cheaper(const WgradArgs& a, const WhCfg& c, int64_t pixels) {
+bool wh_cheaper(const WgradArgs& a, const WhCfg& c, int64_t pixels, double most = kPadMost) {
   auto up = [](int64_t v, int64_t q) { return (v + q - 1) / q * q; };
-  const double here = (double)pixels * up(a.co, 32 * c.ob) * up(a.ci, c.ck) * c.kh * c.kh;
+  double here = (double)pixels * up(a.co, 32 * c.ob) * up(a.ci, c.ck) * c.kh * c.kh;
+  if (pixels > a.m) {
+    if (a.ci <= c.ck) return false;
+    const int64_t blocks = wh_tiles(a, c) * wh_splits(a, c);
+    if (blocks < kWhSlots) here *= (double)kWhSlots / (double)blocks;
+  }
   int64_t rows = up(a.co, 64);
   for (const int b : {96, 128})
     if (up(a.co, b) < rows) rows = up(a.co, b);
-  return here <= kPadMost * (double)a.m * rows * up(a.ktot, 128);
+  return here <= most * (double)a.m * rows * up(a.ktot, 128);
 }
 
 // The configuration for a problem, or ob = 0 where the kernel does not apply.
@@ -468,7 +503,11 @@ WhCfg wgrad_halo_cfg(const WgradArgs& a) {
     // 1x1: steps of 64 consecutive pixels; the largest chunk of 288, 192, 144 or 96 input
     // channels that divides c_in, else of the chunks that cover it in one or two the one that
     // pads it least (12 x 52 x 52 x 256 in one of 288: 22.0 -> 19.7 us; 624 channels in seven of 96
-    // against the general kernel 65.8 -> 79.0)
+    // against the general kernel 65.8 -> 79.0).  Padded, for more than four steps (8 x 8, 224 -> 616:
+    // 5.6 us on the general kernel, 7.4 here; 2 x 13 x 13, 32 -> 640 8.6 and 7.6) that outweigh their
+    // partials (0.9 us a step, 2.5 TB/s; 19 x 19, 528 -> 576 9.5 and 15.5), and in two chunks only
+    // where the general kernel, which fills the GPU from some 32768 pixels up, multiplies as
+    // much (22 x 71 x 71, 392 -> 240 52.4 and 65.1).
     int ck = 0, pad = a.ci;
     for (const int k : {288, 192, 144, 96})
       if (ck == 0 && a.ci % k == 0) ck = k;
@@ -484,7 +523,12 @@ WhCfg wgrad_halo_cfg(const WgradArgs& a) {
     c.pr = 1;
     c.pc = 64;
     c.kh = 1;
-    return pad == a.ci || wh_cheaper(a, c, (int64_t)a.m) ? c : WhCfg{0, 0, 0, 0, 0};
+    if (pad == a.ci) return c;
+    const int64_t steps = wh_npatch(a, c);
+    const bool on = steps > 4 && (steps >= 32 || 0.9 * steps > (double)wh_splits(a, c) * a.co * a.ci * 8 / 2.5e6) &&
+                    (pad == ck || a.m <= 32768 || wh_cheaper(a, c, (int64_t)a.m, 1.0)) &&
+                    wh_cheaper(a, c, (int64_t)a.m);
+    return on ? c : WhCfg{0, 0, 0, 0, 0};
   }
   if (a.kh != 3 || a.kw != 3 || a.ph != 1 || a.pw != 1) return c;
   // offsets within one image (plus its halo) are 32-bit
@@ -507,10 +551,6 @@ WhCfg wgrad_halo_cfg(const WgradArgs& a) {
   c.ob = c.ck == 32 ? wh_ob(a.co) : 2;
   const bool whole = area == (int64_t)a.h * a.w && (pad32 == a.ci || pad48 == a.ci);
   return whole || wh_cheaper(a, c, area * a.n) ? c : WhCfg{0, 0, 0, 0, 0};
-}
-
-int64_t wh_npatch(const WgradArgs& a, const WhCfg& c) {
-  return c.kh == 1 ? (a.m + 63) / 64 : (int64_t)a.n * ((a.h + c.pr - 1) / c.pr) * ((a.w + c.pc - 1) / c.pc);
 }
 
 template <int OB, int CK, int PR, int PC, int S, int KH>
@@ -556,22 +596,7 @@ bool wgrad_halo_plan(const WgradArgs& a, int* splits, int64_t* patches_per_split
   if (c.ob == 0) return false;
   const int64_t npatch = wh_npatch(a, c);
   if (npatch >= (1ll << 30)) return false;
-  const int64_t tiles = (int64_t)((a.co + 32 * c.ob - 1) / (32 * c.ob)) * ((a.ci + c.ck - 1) / c.ck);
-  // Blocks: about 160.  One block fills a CU (all of its LDS and registers), and the
-  // weight gradients run beside the backward's main chain on a second stream: grids that
-  // leave that chain CUs made the two-stream step faster though the kernel alone is slower
-  // (configuration 4 at batch 16: 256 blocks 8.91 ms per step, 192 8.73, 160 8.54, 128
-  // 8.57, against 8.75 with the general kernel on every layer, same host); fewer blocks
-  // also write fewer partials.
-  int64_t slots = 160;
-#ifdef NUMBAT_TUNING
-  if (const char* e = getenv("NUMBAT_WH_SLOTS")) slots = atoi(e);
-#endif
-  int64_t sp = tiles < slots ? slots / tiles : 1;
-  if (sp > npatch) sp = npatch;
-  // partials at most 64 MiB
-  const int64_t part_bytes = (int64_t)a.co * c.kh * c.kh * a.ci * 4;
-  while (sp > 1 && sp * part_bytes > (64ll << 20)) --sp;
+  const int64_t sp = wh_splits(a, c);
   const int64_t pps = (npatch + sp - 1) / sp;
   *patches_per_split = pps;
   *splits = (int)((npatch + pps - 1) / pps);

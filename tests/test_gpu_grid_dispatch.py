@@ -194,7 +194,10 @@ def test_forward_prologue_equals_the_two_calls(shape):
 # 48-channel chunks; all but one row outside), 20 x 8; sizes whose patches' slices would pass it,
 # and the last column, on the general kernel
 @pytest.mark.parametrize("shape", [(2, 52, 52, 64, 80), (2, 45, 48, 88, 96), (3, 22, 32, 144, 40), (5, 41, 16, 32, 64),
-                                   (2, 30, 40, 32, 64), (2, 31, 45, 88, 72), (3, 18, 31, 144, 40), (9, 19, 7, 32, 64)])
+                                   (2, 30, 40, 32, 64), (2, 31, 45, 88, 72), (3, 18, 31, 144, 40), (9, 19, 7, 32, 64),
+                                   # (grids that fill the patch-staged kernel's block slots: 8 x 16, on
+                                   # 96 rows and on 48-channel chunks, and 20 x 8)
+                                   (4, 45, 48, 96, 192), (9, 22, 32, 144, 64), (12, 58, 24, 64, 64)])
 def test_weight_gradient_keeps_infinities_to_their_taps(shape):
     """An infinity in the input's last row and a NaN in its last column reach the gradients of the
     taps that pair them with an output pixel, and no other."""

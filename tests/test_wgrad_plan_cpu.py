@@ -21,3 +21,10 @@ def test_few_pixels_into_large_gradients_stay_whole(c):
 @pytest.mark.parametrize("c", [(2, 32, 32, 16, 32, 3, 1), (1, 100, 98, 88, 128, 3, 2), (8, 14, 14, 592, 144, 3, 1)])
 def test_few_pixels_into_small_gradients_are_split(c):
     assert splits(*c) >= 2
+
+
+def test_patches_past_the_image_need_a_full_grid():
+    """Patches past the last row on 88 tiles, of one split each, would leave most CUs idle: the
+    general kernel splits its pixels.  A padded 1x1 layer of six steps stays whole."""
+    assert splits(7, 242, 8, 704, 216, 3, 1) >= 2
+    assert splits(1, 19, 19, 528, 576, 1, 1) == 0

@@ -736,8 +736,29 @@ bool convhalo_shape(const ConvGemmArgs& a) {
 // two-dimensional (BM / tc) x tc one
 static int halo_pixels(int bm, int tc, int w) { return tc > 0 ? (bm / tc + 2) * (tc + 2) : bm + 2 * w + 2; }
 
+// Whether eight-wave tiles are well filled in whole rounds of 256 and have more than one chunk to
+// walk (18 x 232 x 13, 32 -> 176 columns: 20.4 us, 17.0 on 128-row tiles, whose blocks overlap)
+static bool linear256_fills(int64_t tiles256, int cs) {
+  const int64_t rounds = (tiles256 + 255) / 256;
+  return cs > 32 && (double)tiles256 / (double)(256 * rounds) >= (rounds > 1 ? 0.75 : 0.66);
+}
+// 96 or 64 columns per tile (3 or 2): 96 for their multiples (of a forward from 256 tiles up: 9 x 23 x
+// 23, 176 -> 192 16.8 us, 14.0 on 64 columns); other counts take the one with less work per CU (its
+// most tiles times their columns) unless eight-wave tiles of 96 fill their rounds.  Data gradients, us, 64 against 96 columns: 14 x 14, 136 <- 64 6.7 : 8.4, 22 x 29 x 29, 152 <-
+// 80 11.4 : 13.5, 4 x 53 x 53, 560 <- 64 15.7 : 18.0; forward 14 x 28 x 28, 128 -> 272 17.5 : 20.2; 16 x 80 x
+// 80, 192 -> 80 52.0 : 39.9.
+static int halo_columns(int64_t m, int nout, int cs, int w, bool bt) {
+  const int64_t c96 = (nout + 95) / 96, c64 = (nout + 63) / 64;
+  if (c96 * 96 > c64 * 64) return 2;
+  const int64_t t256 = (m + 255) / 256, rows = w > 63 ? t256 : (m + 127) / 128;
+  if (nout % 96 == 0 && (bt || w > 63 || rows * c96 >= 256)) return 3;
+  if (w <= 63 && linear256_fills(t256 * c96, cs)) return 3;
+  if (w > 63 && w <= 95 && t256 * c96 >= 100 && t256 * c96 <= 256) return 3;
+  return (rows * c64 + 255) / 256 * 64 < (rows * c96 + 255) / 256 * 96 ? 2 : 3;
+}
+
 // Halo kernel tile, from a sweep of the instantiations over the detector's 3x3 stride-1
-// layers at batch 16 (each layer alone): 96 columns unless 64 pad the channel count less;
+// layers at batch 16 (each layer alone): 96 or 64 columns (halo_columns);
 // images up to 63 pixels wide on 128-row tiles with a whole tap row (three taps) per
 // step and two weight stages (40 x 40, 192 channels: forward 33.6 -> 29.6 us, data
 // gradient 29.4 -> 24.0), up to 95 wide on 256-row tiles with one tap per step and three
@@ -749,11 +770,12 @@ static int halo_pixels(int bm, int tc, int w) { return tc > 0 ? (bm / tc + 2) * 
 // with a tap row per step 10-20% slower, and 8 x 16 tiles on the 80-wide layers 13-18%
 // slower than their linear 256-row tiles).  Fewer than 160 256-row tiles leave CUs idle:
 // images of 64 to 95 columns then take 128-row tiles.  Forward grids of fewer than 256 tiles
-// keep the direct-to-LDS kernel on two-dimensional tiles and where 64 tiles or more walk a
-// long reduction (16 images of 20 x 20, 576 -> 192: 31.0 against 35.3 us; 288 -> 288: the
-// layer's training pass 96.2 against 101.7 us); elsewhere the halo kernel is as fast or
-// faster (one image of 40 x 40, 24 -> 72: 6.1 us, and 10.7 on the register-staged kernel; 4
-// of 26 x 26 x 128: 8.2 and 11.5; 8 of 40 x 40 x 192: 15.0 and 20.0).  Returns variant kVariantGeneric when the halo
+// keep the direct-to-LDS kernel on two-dimensional tiles, where 64 tiles or more walk a long
+// reduction (16 images of 20 x 20, 576 -> 192: 31.0 against 35.3 us; 288 -> 288: the layer's
+// training pass 96.2 against 101.7 us) and on 64 to 95 columns up to 32 channels, to 64 below
+// 160 tiles (2 x 76 x 76, 48 -> 288 10.1 against 12.1 us); elsewhere the halo kernel is as fast or
+// faster (4 images of 26 x 26 x 128: 8.2 us against 11.5, 8 of 40 x 40 x 192: 15.0 and 20.0).
+// Returns variant kVariantGeneric when the halo
 // kernel is not used.
 //
 // Linear 256 x 96 tiles of eight waves (one block per CU): a wave's 64 x 96 share needs 5 LDS
@@ -770,7 +792,7 @@ static int halo_pixels(int bm, int tc, int w) { return tc > 0 ? (bm / tc + 2) * 
 // pro_bwd: the tile of the backward prologue, whose sums have the plain kernel's order on
 // 128-row tiles too.
 TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool any_grid, bool pro_bwd) {
-  const int tn = (nout + 95) / 96 * 96 <= (nout + 63) / 64 * 64 ? 3 : 2;
+  const int tn = halo_columns(m, nout, cs, w, bt);
   const int64_t cols = (nout + 32 * tn - 1) / (32 * tn), tiles256 = (m + 255) / 256 * cols;
   HInst want{2, tn, 0, 1, 3, 0, 1};
   if (w > 95) {
@@ -780,9 +802,7 @@ TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool a
     if (tn == 3 && tiles256 >= 100 && tiles256 <= 256) want = pro_bwd ? HInst{1, 3, 0, 3, 2, 0, 2} : HInst{2, 3, 0, 3, 2, 0, 2};
     else if (tiles256 < 160) want = HInst{1, tn, 0, 3, 2, 0, 2};
   } else {
-    const int64_t rounds = (tiles256 + 255) / 256;
-    const double fill = (double)tiles256 / (double)(256 * rounds);
-    want = tn == 3 && fill >= (rounds > 1 ? 0.75 : 0.66) && !pro_bwd ? HInst{2, 3, 0, 3, 3, 0, 2} : HInst{1, tn, 0, 3, 2, 0, 2};
+    want = tn == 3 && linear256_fills(tiles256, cs) && !pro_bwd ? HInst{2, 3, 0, 3, 3, 0, 2} : HInst{1, tn, 0, 3, 2, 0, 2};
   }
   const TileCfg none{0, 0, -1, kVariantGeneric};
   const int bm = 128 * want.tm;
@@ -790,7 +810,13 @@ TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool a
   const int64_t tiles = ((m + bm - 1) / bm) * cols;
   // (of 256-row tiles half as many cover the grid that 256 of 128 rows do)
   const int64_t full = linear256(want) ? 128 : 256;
+  // (one chunk of at most 24 channels: the gather of taps is as cheap as the halo.  16 x 219 x 24,
+  // 16 -> 8: 14.5 us, 11.2 on the direct-to-LDS kernel, 10 x 159 x 11, 16 -> 336 17.2 and 14.7; 8
+  // channels, which that kernel does not take, past two blocks per CU: 18 x 54 x 54, 8 -> 112 17.5 us,
+  // 15.3 on the register-staged kernel, but 23 x 73 x 73, 8 -> 16 12.6 and 14.7)
+  if (!bt && !any_grid && w <= 95 && cs < 32 && (cs > 8 || tiles > 512)) return none;
   if (!bt && !any_grid && tiles < full && (want.tc > 0 || (cs >= 256 && tiles >= full / 4))) return none;
+  if (!bt && !any_grid && w > 63 && cs <= 64 && tiles256 < (cs <= 32 ? 256 : 160)) return none;
   int best = -1;
   for (int i = 0; i < kNumH; ++i) {
     const HInst& c = kH[i];

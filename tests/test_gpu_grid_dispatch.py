@@ -32,7 +32,7 @@ CASES = [
     # columns, two-dimensional tiles), direct-to-LDS (1x1, stride 2, more than 32768 rows)
     (2, 30, 30, 24, 72, 3, 1), (2, 12, 62, 8, 16, 3, 1), (1, 21, 70, 40, 56, 3, 1), (1, 64, 96, 24, 40, 3, 1),
     (2, 35, 35, 104, 80, 1, 1), (2, 31, 29, 24, 40, 3, 2), (4, 190, 190, 88, 24, 3, 2), (2, 140, 130, 24, 56, 1, 1), (2, 19, 17, 56, 88, 1, 1),
-    # 96-column halo tiles for 80 channels
+    # two halo tiles of 64 columns for 80 channels
     (2, 33, 41, 64, 80, 3, 1),
     # patch-staged weight gradient past the image and the channels: 52 x 52 on 20 x 4, 13 x 37,
     # 72 of 96 and 40 of 64 rows; 1x1 chunks of which the last ends early
@@ -46,6 +46,10 @@ CASES = [
     # eight-wave direct-to-LDS tiles: 256 x 192, 256 x 128 (1x1 and stride 2) and 128 x 128
     (5, 57, 57, 264, 576, 1, 1), (5, 60, 60, 576, 40, 1, 1), (5, 75, 75, 256, 248, 1, 1), (10, 95, 94, 40, 248, 3, 2),
     (3, 37, 37, 72, 576, 1, 1), (2, 50, 58, 640, 48, 1, 1),
+    # 80 columns as one tile of 96 (as two of 64 above)
+    (12, 40, 40, 40, 80, 3, 1),
+    # short reductions into many rows on tiles of 96 and 128 columns
+    (1, 190, 190, 16, 168, 1, 1), (1, 190, 190, 104, 24, 1, 1),
 ]
 IDS = ["n{}h{}w{}ci{}co{}k{}s{}".format(*c) for c in CASES]
 

@@ -953,12 +953,13 @@ bool convgemm_taps(ConvGemmArgs& a, int bm) {
 // the products.  One block per CU, so the grid has to fill whole rounds of 256 blocks: the
 // tile is taken where the GEMM's own area is at least a share `eff` of the rounds' area and
 // nout fills its columns to 10%.  Measured, us, against the rule below it:
-//  forward (eff 0.6, reductions of 256 or more): 16 x 40 x 40, 960 -> 384 (0.78) 33.7 -> 29.0, 80 x
+//  forward (eff 0.6, reductions of 256 or more, past two rounds of 512): 16 x 40 x 40, 960 -> 384 (0.78) 33.7 -> 29.0, 80 x
 //   80, 576 -> 192 (0.78) 63.4 -> 48.2, 160 x 160 stride 2, 96 -> 192 (0.78) 64.5 -> 55.9; 12 x 52 x 52 x
 //   256 on 256 x 128 (0.99) 17.8 -> 12.1, 100 x 100 stride 2, 64 -> 128 (0.61) 19.6 -> 14.0; 40 x 40 x 320
 //   (0.65, a sixth of the columns idle) 15.1 -> 16.4.  Short reductions are bound by memory, and
 //   one block per CU overlaps its output with nothing: training passes of 80 x 80 x 192 148.8
-//   -> 150.8, 32 images of 80 x 80 x 128 170.2 -> 175.3
+//   -> 150.8, 32 images of 80 x 80 x 128 170.2 -> 175.3; past two
+//   rounds below 512: 5 x 229 x 229, 400 -> 352 174 -> 196
 //  data gradient (eff 0.8, at most two rounds; the weights' transposing reads cost more): 40 x
 //   40, 960 <- 384 (0.98) 35.6 -> 33.1, 52 x 52 x 256 (0.99) 14.5 -> 10.7; 40 x 40, 768 <- 384 (0.78) 28.8 ->
 //   30.2; six rounds, 4 x 125 x 144, 624 <- 272, the training pass 283.9 -> 287.4
@@ -972,7 +973,7 @@ TileCfg wide_pick(int64_t m, int nout, int ktot, bool bt) {
   constexpr int kT[2][3] = {{256, 192, kWide256x192}, {256, 128, kWide256x128}};
   for (const auto& t : kT) {
     const int64_t cols = (nout + t[1] - 1) / t[1], tiles = (m + t[0] - 1) / t[0] * cols, rounds = (tiles + 255) / 256;
-    if (cols * t[1] * 10 > (int64_t)nout * 11 || (bt ? rounds > 2 : ktot < 256)) continue;
+    if (cols * t[1] * 10 > (int64_t)nout * 11 || (bt ? rounds > 2 : ktot < (rounds > 2 ? 512 : 256))) continue;
     const double eff = (double)m * nout / ((double)rounds * 256 * t[0] * t[1]);
     if (eff >= best_eff) {
       best_eff = eff;
@@ -1019,6 +1020,11 @@ TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, boo
     }
   }
   const bool fast = !generic && dma_channels(cs, kVariantDma32);
+  // Channel counts that are no multiple of 16 or below 32, which the 64 columns below were not
+  // fitted on, keep the least padding where 64 columns pad over a fifth more: 16 x 219 x 219
+  // stride 2, 88 <- 24 122 us, and 87 on 96 columns; 2 x 149 x 149, 824 -> 88 262 and 150.
+  const bool unfitted = cs % 16 != 0 || cs < 32;
+  const bool narrower64 = unfitted && (int64_t)(nout + 63) / 64 * 64 * 5 > (int64_t)((nout + bn - 1) / bn) * bn * 6;
   if (fast && cs >= 32 && nphase == 1) {
     const TileCfg t = wide_pick(m_max, nout, ktot, bt);
     if (t.variant == kVariantWide) return t;
@@ -1027,7 +1033,7 @@ TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, boo
   if (fast && !bt) {
     const int64_t mt = (m_max + 127) / 128;
     const int64_t blocks128 = mt * ((nout + bn - 1) / bn);
-    if (blocks128 < 400 && bn > 64) bn = 64;
+    if (blocks128 < 400 && bn > 64 && !narrower64) bn = 64;
     bm = 128;
     if (m_max > 32768) {
       variant = kVariantDma32;
@@ -1046,10 +1052,11 @@ TileCfg convgemm_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, boo
       variant = mt * ((nout + 63) / 64) > 256 ? kVariantDma2 : kVariantDma3;
     }
   } else if (fast) {
-    // (channel counts that are no multiple of 16 or below 32 keep the least padding where 64
-    // columns pad over a fifth more: 16 x 219 x 219 stride 2, 88 <- 24: 122 us, and
-    // 87 on 96 columns)
-    const bool least = (cs % 16 != 0 || cs < 32) && (int64_t)(nout + 63) / 64 * 64 * 5 > (int64_t)((nout + bn - 1) / bn) * bn * 6;
+    // (so do they on short reductions into many rows that are no whole 64-byte lines, where the
+    // output is the work and neighbouring tiles share its lines: 14 x 65 x 239, 216 <- 40 73.2 us ->
+    // 45.2, 26 x 86 x 86 stride 2, 600 <- 16 168 -> 118, 16 x 143 x 143 stride 2, 104 <- 40 55.5 -> 39.7; whole
+    // lines 4 x 151 x 132 stride 2, 896 <- 16 36.0 on 64 columns, 46.2 on 128)
+    const bool least = narrower64 || (unfitted && nout % 32 != 0 && ktot <= 256 && m_max > (nphase > 1 ? 8192 : 32768));
     const int bn64 = bn < 64 || least ? bn : 64;
     bm = 128;
     if (m_max > 32768) {

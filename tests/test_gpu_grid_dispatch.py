@@ -99,7 +99,14 @@ def test_conv_passes(i):
     assert_close(blocks.host_f64(dwa), 2 * dwref, "dw accumulated", 1e-5)
 
 
-@pytest.mark.parametrize("i", [0, 1, 4, 5, 10], ids=[IDS[i] for i in (0, 1, 4, 5, 10)])
+# split tiles and a halo tile; eight-wave halo tiles, linear (two widths) and two-dimensional;
+# 256 x 192, 256 x 128 and 128 x 128 direct-to-LDS tiles
+INFER = [0, 1, 4, 5, 10] + [CASES.index(c) for c in ((9, 40, 41, 48, 288, 3, 1), (3, 70, 71, 40, 288, 3, 1),
+                                                     (8, 160, 160, 16, 64, 3, 1), (5, 57, 57, 264, 576, 1, 1),
+                                                     (5, 75, 75, 256, 248, 1, 1), (3, 37, 37, 72, 576, 1, 1))]
+
+
+@pytest.mark.parametrize("i", INFER, ids=[IDS[i] for i in INFER])
 def test_inference_outputs(i):
     """The bias and the evaluation-mode BN + SiLU output stages on those tiles."""
     n, h, w, ci, co, k, st = CASES[i]

@@ -153,7 +153,8 @@ numbat_status numbat_conv_fwd(const numbat_conv_problem* p, const void* x, const
  * by numbat_conv_fwd bit for bit wherever that forward runs the same kernel (3x3 problems
  * whose grid has at least 256 tiles).  Supported: 3x3, stride 1, pad 1, c_in a multiple of
  * 16 in 32 .. 1024, images the 3x3 stride-1 kernel takes (up to 95 wide, or a multiple of
- * 32 wide and 8 high); otherwise NUMBAT_ERR_UNSUPPORTED before any launch. */
+ * 32 wide and 8 high), x_pixel_strides that keep a tile's halo within 31-bit byte offsets;
+ * otherwise NUMBAT_ERR_UNSUPPORTED before any launch. */
 numbat_status numbat_conv_fwd_bn_silu_prologue(const numbat_conv_problem* p, const void* y_prev,
                                                const float* prev_stats, const float* gamma, const float* beta,
                                                float eps, const void* w, void* y, float* batch_stats, void* ws,
@@ -218,7 +219,8 @@ numbat_status numbat_conv_bwd_data(const numbat_conv_problem* p, const void* dy,
  * aligned with pixel strides multiples of 8.  No workspace.  Returns NUMBAT_ERR_UNSUPPORTED
  * unless the problem is 3x3, stride 1, padding 1, c_out a multiple of 16 in 32 .. 1024,
  * c_in a multiple of 8, on an image the halo kernel takes (numbat_workspace_size with
- * NUMBAT_OP_CONV_BWD_DATA_BN_SILU answers that without a launch). */
+ * NUMBAT_OP_CONV_BWD_DATA_BN_SILU answers that without a launch), with pixel strides (g's too)
+ * that keep a tile's halo within 31-bit byte offsets. */
 numbat_status numbat_conv_bwd_data_bn_silu_prologue(const numbat_conv_problem* p, const void* g,
                                                     int64_t g_pixel_stride, const void* y, const float* save_mean,
                                                     const float* save_rstd, const float* gamma, const float* beta,

@@ -187,13 +187,15 @@ bool halo_geometry(const ConvDesc& d) {
 #endif
   return on;
 }
+// whether the halo of a tile t, of pixel stride pix, is within 31-bit byte offsets
+bool halo_in_range(const ConvDesc& d, const TileCfg& t, int64_t pix) {
+  return t.variant == kVariantHalo && convhalo_last_pixel(t, d.w) * pix * 2 + 64 <= 0x7ffffff0;
+}
 TileCfg halo_tile(const ConvDesc& d, int cs, int nout, bool bt, bool pro_bwd = false) {
-  const int64_t pix2 = (bt ? d.y_pix : d.x_pix) * 2;
-  // (a tile's halo, of at most 256 + 2 w + 2 or 10 w + 34 pixels, within 31-bit byte offsets)
-  if (!halo_geometry(d) || cs % 8 != 0 || (int64_t)nout * 9 * cs * 2 >= ((int64_t)1 << 31) - 16 ||
-      (10ll * d.w + 258) * pix2 >= (1ll << 31) - (1ll << 25))
-    return TileCfg{0, 0, -1, kVariantGeneric};
-  return convhalo_pick(d.m, nout, cs, d.h, d.w, bt, false, pro_bwd);
+  const TileCfg none{0, 0, -1, kVariantGeneric};
+  if (!halo_geometry(d) || cs % 8 != 0 || (int64_t)nout * 9 * cs * 2 >= ((int64_t)1 << 31) - 16) return none;
+  const TileCfg t = convhalo_pick(d.m, nout, cs, d.h, d.w, bt, false, pro_bwd);
+  return halo_in_range(d, t, bt ? d.y_pix : d.x_pix) ? t : none;
 }
 
 // the geometry of the forward's GEMM (pointers and output options are the launch's)
@@ -379,7 +381,8 @@ TileCfg prologue_tile(const ConvDesc& d) {
   if (!halo_geometry(d) || narrow(d) || d.ci % 16 != 0 || d.ci < 32 || d.ci > kProMaxC ||
       (int64_t)d.co * 9 * d.ci * 2 >= ((int64_t)1 << 31) - 16)
     return TileCfg{0, 0, -1, kVariantGeneric};
-  return convhalo_pick(d.m, d.co, d.ci, d.h, d.w, false, true);
+  const TileCfg t = convhalo_pick(d.m, d.co, d.ci, d.h, d.w, false, true);
+  return halo_in_range(d, t, d.x_pix) ? t : TileCfg{0, 0, -1, kVariantGeneric};
 }
 
 // the data gradient with the BN + SiLU backward prologue: the halo kernel's tile for the
@@ -989,6 +992,9 @@ numbat_status numbat_conv_bwd_data_bn_silu_prologue(const numbat_conv_problem* p
     return conv_bwd_data_launch(d, dy, w, dx, accumulate, nullptr, stream);
   }
   ConvGemmArgs a = halo_dgrad_args(d, g, g_pix, w, dx, accumulate);
+  const TileCfg t = bwd_prologue_tile(d);
+  if (!halo_in_range(d, t, g_pix))
+    return fail(NUMBAT_ERR_UNSUPPORTED, "g_pixel_stride %lld puts a tile's halo beyond 31-bit offsets", (long long)g_pix);
   a.pro_kind = kProBwd;
   a.pro_gamma = gamma;
   a.pro_beta = beta;
@@ -1000,7 +1006,7 @@ numbat_status numbat_conv_bwd_data_bn_silu_prologue(const numbat_conv_problem* p
   a.pro_y_pix = d.y_pix;
   a.pro_dy = static_cast<bf16_t*>(dy);
   a.pro_m = d.m;
-  const hipError_t e = convhalo_launch(a, bwd_prologue_tile(d), static_cast<hipStream_t>(stream), KC_CONV_DGRAD);
+  const hipError_t e = convhalo_launch(a, t, static_cast<hipStream_t>(stream), KC_CONV_DGRAD);
   if (e != hipSuccess) return hip_fail(e, "data-gradient launch");
   return ok();
 }

@@ -828,6 +828,11 @@ TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool a
   return TileCfg{128 * kH[best].tm, 32 * kH[best].tn, best, kVariantHalo};
 }
 
+int64_t convhalo_last_pixel(const TileCfg& t, int w) {
+  const int tc = kH[t.id].tc;
+  return tc > 0 ? (int64_t)(t.bm / tc + 1) * w + tc + 1 : (int64_t)t.bm + 2 * (int64_t)w + 1;
+}
+
 hipError_t convhalo_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_t s, int cls) {
   if (t.variant != kVariantHalo || t.id < 0 || t.id >= kNumH || !convhalo_shape(a)) return hipErrorInvalidValue;
   if (a.pro_kind == kProFwd && (a.bt || a.cs > kProMaxC || a.pro_mean == nullptr)) return hipErrorInvalidValue;

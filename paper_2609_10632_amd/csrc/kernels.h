@@ -157,7 +157,7 @@ bool convgemm_taps(ConvGemmArgs& a, int bm);
 TileCfg convsplit_pick(int64_t m_max, int nout, int cs, int ktot, int nphase, bool bt);
 hipError_t convsplit_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_t s, int cls);
 // 3x3, stride-1, padding-1 convolutions whose input halo is staged in LDS once per
-// 32-channel chunk (conv_gemm.hip, convhalo_kernel): the forward (K-major weights, taps in
+// 32-channel chunk (conv_halo.hip, convhalo_kernel): the forward (K-major weights, taps in
 // off[]) and the data gradient (bt: the OHWI weights read in place, flipped; off[] unused).
 // convhalo_shape: whether the kernel takes the problem; convhalo_pick: its tile for m rows,
 // nout columns, cs source channels and an h x w image, bt for the data gradient, any_grid to
@@ -165,6 +165,8 @@ hipError_t convsplit_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_t
 bool convhalo_shape(const ConvGemmArgs& a);
 TileCfg convhalo_pick(int64_t m, int nout, int cs, int h, int w, bool bt, bool any_grid = false,
                       bool pro_bwd = false);
+// the last halo pixel of a tile t of a w-wide image, from its first
+int64_t convhalo_last_pixel(const TileCfg& t, int w);
 hipError_t convhalo_launch(const ConvGemmArgs& a, const TileCfg& t, hipStream_t s, int cls);
 // forward convolution of a narrow input (cs = ci < 8, one phase, wt = OHWI weights with
 // K = taps * ci packed densely); rows per tile and columns per tile of narrow_pick

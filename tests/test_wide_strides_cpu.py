@@ -56,3 +56,26 @@ def test_backward_prologue_without_a_workspace(c):
     assert device_error(nb.numbat_conv_bwd_data_bn_silu_prologue, p, *([FAKE] * 11)).startswith("data-gradient launch")
     # the halo kernel is the data gradient's own too
     assert bwd_data(p).startswith("data-gradient launch")
+
+
+@pytest.mark.parametrize("n,h,w,ci,co,last", [(1, 20, 20, 288, 48, 169), (1, 16, 70, 96, 64, 269), (1, 8, 96, 64, 48, 897)])
+def test_prologues_up_to_the_halo_of_their_tile(n, h, w, ci, co, last):
+    """The prologue entries have no other kernel to fall back on: they take every pixel stride with
+    which the last halo pixel of their own tile is within 31-bit byte offsets, and refuse the
+    first that is not (`last`: that pixel, from the tile's first)."""
+    fits = (0x7ffffff0 - 64) // (2 * last) // 8 * 8
+    for stride in (fits - 8, fits + 8):
+        ok = stride < fits
+        p = nb.conv_problem(n, h, w, ci, co, 3, y_pixel_stride=stride)
+        q = nb.conv_problem(n, h, w, co, ci, 3, x_pixel_stride=stride)
+        bwd = (nb.numbat_conv_bwd_data_bn_silu_prologue, p, *([FAKE] * 11))
+        fwd = (nb.numbat_conv_fwd_bn_silu_prologue, q, FAKE, FAKE, FAKE, FAKE, 1e-3, FAKE, FAKE)
+        # (the incoming gradient's own pixel stride)
+        g = (nb.numbat_conv_bwd_data_bn_silu_prologue, nb.conv_problem(n, h, w, ci, co, 3), *([FAKE] * 11))
+        for (fn, *args), kw in ((bwd, {}), (fwd, {}), (g, {"g_pixel_stride": stride})):
+            if ok:
+                device_error(fn, *args, **kw)
+            else:
+                with pytest.raises(nb.NumbatError) as ei:
+                    fn(*args, **kw)
+                assert ei.value.status == nb.ERR_UNSUPPORTED, ei.value

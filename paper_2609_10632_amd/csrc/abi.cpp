@@ -368,9 +368,10 @@ TileCfg fwd_tile(const ConvDesc& d) {
   const int ktot = d.kh * d.kw * d.ci;
   if (t.variant != kVariantHalo) t = convgemm_pick(d.m, d.co, d.ci, ktot, 1, false);
   // Channel counts that also run on the register-staged kernel (not a multiple of 16, or below
-  // 32) take its 256-row tiles where only those keep the statistics partials within
+  // 32) take its 256-row tiles where those, and not t's, keep the statistics partials within
   // numbat_conv_fwd_noalloc's scratch.
-  if ((d.ci % 16 != 0 || d.ci < 32) && with_header(stats_bytes(d, t.bm)) > kScratchBytes)
+  if ((d.ci % 16 != 0 || d.ci < 32) && t.bm < 256 && with_header(stats_bytes(d, t.bm)) > kScratchBytes &&
+      with_header(stats_bytes(d, 256)) <= kScratchBytes)
     return convgemm_pick(d.m, d.co, d.ci, ktot, 1, false, true);
   return t;
 }
@@ -991,10 +992,10 @@ numbat_status numbat_conv_bwd_data_bn_silu_prologue(const numbat_conv_problem* p
     if (e != hipSuccess) return hip_fail(e, "BN+SiLU backward launch");
     return conv_bwd_data_launch(d, dy, w, dx, accumulate, nullptr, stream);
   }
-  ConvGemmArgs a = halo_dgrad_args(d, g, g_pix, w, dx, accumulate);
   const TileCfg t = bwd_prologue_tile(d);
   if (!halo_in_range(d, t, g_pix))
     return fail(NUMBAT_ERR_UNSUPPORTED, "g_pixel_stride %lld puts a tile's halo beyond 31-bit offsets", (long long)g_pix);
+  ConvGemmArgs a = halo_dgrad_args(d, g, g_pix, w, dx, accumulate);
   a.pro_kind = kProBwd;
   a.pro_gamma = gamma;
   a.pro_beta = beta;

@@ -19,3 +19,13 @@ def test_partials_fit_the_static_scratch(c):
     rows = -(-n * ho * wo // 256)
     assert rows * co * 8 + 512 <= SCRATCH  # what 256-row tiles need
     assert nb.numbat_workspace_size(nb.OP_CONV_FWD, p) <= SCRATCH
+
+
+# 256-row partials past the scratch too: nothing is gained on other tiles, so such a problem keeps the
+# 128-row tiles of the kernel it would take without the limit
+@pytest.mark.parametrize("c", [(400, 60, 60, 40, 400, 1, 1), (400, 60, 60, 24, 400, 1, 1)])
+def test_partials_past_the_static_scratch(c):
+    n, h, w, ci, co, k, s = c
+    p = nb.conv_problem(n, h, w, ci, co, k, stride=s)
+    assert -(-n * h * w // 256) * co * 8 > SCRATCH
+    assert nb.numbat_workspace_size(nb.OP_CONV_FWD, p) >= -(-n * h * w // 128) * co * 8

@@ -389,11 +389,14 @@ TRAFFIC_PROFILES = {
                              ("paper_2609_10632_amd/csrc/conv_wgrad.hip", "paper_2609_10632_amd/csrc/conv_wgrad_halo.hip",
                               "paper_2609_10632_amd/csrc/common.h", "paper_2609_10632_amd/csrc/kernels.h")),
     ("conv_fwd_igemm", 4, 16): ("profiles/conv_fwd_igemm_c4_b16_traffic.md",
-                                ("paper_2609_10632_amd/csrc/conv_gemm.hip", "paper_2609_10632_amd/csrc/common.h",
-                                 "paper_2609_10632_amd/csrc/kernels.h")),
+                                ("paper_2609_10632_amd/csrc/conv_gemm.hip", "paper_2609_10632_amd/csrc/conv_halo.hip",
+                                 "paper_2609_10632_amd/csrc/conv_split.hip", "paper_2609_10632_amd/csrc/conv_tile.h",
+                                 "paper_2609_10632_amd/csrc/common.h", "paper_2609_10632_amd/csrc/kernels.h")),
     ("conv_dgrad_igemm", 4, 16): ("profiles/conv_dgrad_igemm_c4_b16_traffic.md",
-                                  ("paper_2609_10632_amd/csrc/conv_gemm.hip", "paper_2609_10632_amd/csrc/conv_aux.hip",
-                                   "paper_2609_10632_amd/csrc/common.h", "paper_2609_10632_amd/csrc/kernels.h")),
+                                  ("paper_2609_10632_amd/csrc/conv_gemm.hip", "paper_2609_10632_amd/csrc/conv_halo.hip",
+                                   "paper_2609_10632_amd/csrc/conv_split.hip", "paper_2609_10632_amd/csrc/conv_tile.h",
+                                   "paper_2609_10632_amd/csrc/conv_aux.hip", "paper_2609_10632_amd/csrc/common.h",
+                                   "paper_2609_10632_amd/csrc/kernels.h")),
 }
 
 

@@ -5,8 +5,8 @@
 // Kernels:
 //  * convdma_kernel, for source channel counts that are multiples of 8 and at least 16 (every
 //    layer of the detector but the image input): both operands reach LDS through loads that
-//    write LDS directly, in 2 to 4 stages (up to 6 supported), with 4 or 8 waves split along M or, on tiles of up to
-//    256 x 192 outputs, eight waves in four rows of two;
+//    write LDS directly, in 2 to 4 stages, with 4 or 8 waves split along M or, on tiles of up
+//    to 256 x 192 outputs, eight waves in four rows of two;
 //  * convgemm_kernel, for any other channel count that is a multiple of 8 (and tiles
 //    whose address span exceeds 31 bits): each wave loads its own MFMA A fragments (16
 //    contiguous bytes per lane) from global memory into a register ring several steps
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(NW * 64) void convdma_kernel(ConvGemmArgs a) {
   using Sh = DmaShape<TM, TN, S, BK, NW, WN, BT>;
   constexpr int BM = G::BM, BN = G::BN, WTM = G::WTM;
   constexpr int AI = Sh::AI, BI = Sh::BI, BI_MAX = Sh::BI_MAX, RPI = Sh::RPI, CPR = Sh::CPR, WIN = Sh::WIN;
-  static_assert(S >= 2 && S <= 6, "2..6 LDS stages");
+  static_assert(S >= 2 && S <= 4, "2..4 LDS stages");
   static_assert(BK == 32 || BK == 64, "stage depth");
   static_assert(Sh::PENDING <= 63, "load counter range");
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
@@ -307,14 +307,10 @@ __global__ __launch_bounds__(NW * 64) void convdma_kernel(ConvGemmArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t sA1[Sh::A_ELEMS];
   __shared__ __attribute__((aligned(16))) bf16_t sA2[Sh::A_ELEMS];
   __shared__ __attribute__((aligned(16))) bf16_t sA3[Sh::A_ELEMS];
-  __shared__ __attribute__((aligned(16))) bf16_t sA4[S > 4 ? Sh::A_ELEMS : 8];
-  __shared__ __attribute__((aligned(16))) bf16_t sA5[S > 5 ? Sh::A_ELEMS : 8];
   __shared__ __attribute__((aligned(16))) bf16_t sB0[Sh::B_ELEMS];
   __shared__ __attribute__((aligned(16))) bf16_t sB1[Sh::B_ELEMS];
   __shared__ __attribute__((aligned(16))) bf16_t sB2[Sh::B_ELEMS];
   __shared__ __attribute__((aligned(16))) bf16_t sB3[Sh::B_ELEMS];
-  __shared__ __attribute__((aligned(16))) bf16_t sB4[S > 4 ? Sh::B_ELEMS : 8];
-  __shared__ __attribute__((aligned(16))) bf16_t sB5[S > 5 ? Sh::B_ELEMS : 8];
   __shared__ int64_t s_dst[BM];
   __shared__ float s_red[G::WM][BN];
   __shared__ float s_mean[BN];
@@ -323,18 +319,14 @@ __global__ __launch_bounds__(NW * 64) void convdma_kernel(ConvGemmArgs a) {
     if constexpr (s == 0) return sA0;
     else if constexpr (s == 1) return sA1;
     else if constexpr (s == 2) return sA2;
-    else if constexpr (s == 3) return sA3;
-    else if constexpr (s == 4) return sA4;
-    else return sA5;
+    else return sA3;
   };
   auto stage_b = [&](auto sc) __attribute__((always_inline)) -> bf16_t* {
     constexpr int s = decltype(sc)::value;
     if constexpr (s == 0) return sB0;
     else if constexpr (s == 1) return sB1;
     else if constexpr (s == 2) return sB2;
-    else if constexpr (s == 3) return sB3;
-    else if constexpr (s == 4) return sB4;
-    else return sB5;
+    else return sB3;
   };
 
   // (launch order: the XCD-aware order measured no faster for these GEMMs; a constant
@@ -862,22 +854,6 @@ hipError_t launch_g(const ConvGemmArgs& a, int variant, hipStream_t s) {
     launch_dma<c.tm, c.tn, 3, 32, 4>(a, mmax, s);
   else if (variant == kVariantDma3W8 && c.tn <= 4)
     launch_dma<1, c.tn <= 4 ? c.tn : 4, 3, 64, 8>(a, mmax, s);
-#if defined(NUMBAT_TUNING) && NUMBAT_TUNING > 1
-  else if (variant == 6)
-    launch_dma<c.tm, c.tn, 4, 32, 4>(a, mmax, s);
-  else if (variant == 8 && c.tn <= 4)
-    launch_dma<1, c.tn <= 4 ? c.tn : 4, 2, 64, 8>(a, mmax, s);
-  else if (variant == 9 && c.tn <= 4)
-    launch_dma<1, c.tn <= 4 ? c.tn : 4, 4, 32, 8>(a, mmax, s);
-  else if (variant == 10 && c.tn <= 4)
-    launch_dma<1, c.tn <= 4 ? c.tn : 4, 3, 32, 8>(a, mmax, s);
-  else if (variant == 12 && c.tm == 1 && c.tn <= 3)
-    launch_dma<1, c.tn <= 3 ? c.tn : 3, 5, 64, 4>(a, mmax, s);
-  else if (variant == 13 && c.tm == 1 && c.tn <= 2)
-    launch_dma<1, c.tn <= 2 ? c.tn : 2, 6, 64, 4>(a, mmax, s);
-  else if (variant == 14 && c.tm == 1)
-    launch_dma<1, c.tn, 6, 32, 4>(a, mmax, s);
-#endif
   else {
     dim3 grid((unsigned)((mmax + Sh::BM - 1) / Sh::BM), (unsigned)((a.nout + Sh::BN - 1) / Sh::BN),
               (unsigned)a.nphase);

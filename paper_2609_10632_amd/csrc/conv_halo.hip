@@ -48,7 +48,7 @@ struct HaloShape {
   static constexpr int BI_MIN = BI / NW, BI_MAX = (BI + NW - 1) / NW;
   static_assert(KT == 1 || KT == 3, "one tap or one tap row per step");
   static_assert((2 * SPC) % SB == 0, "stage of a step known at compile time over two chunks");
-  static_assert(SB >= 2 && SB - 1 <= SPC, "prefetch within one chunk");
+  static_assert(SB >= 2 && SB <= 3 && SB - 1 <= SPC, "prefetch within one chunk");
   // two-dimensional tiles (TC > 0): TR x TC output pixels of one image, whose padded halo of
   // (TR + 2) x (TC + 2) pixels fits the buffer
   static constexpr int TR = TC > 0 ? G::BM / TC : 0;
@@ -103,9 +103,6 @@ __global__ __launch_bounds__(256 * KV, halo_min_waves(TC, PRO, KV, KP)) void con
   __shared__ __attribute__((aligned(16))) unsigned char sB0[KT * TBYTES];
   __shared__ __attribute__((aligned(16))) unsigned char sB1[KT * TBYTES];
   __shared__ __attribute__((aligned(16))) unsigned char sB2[SB > 2 ? KT * TBYTES : 16];
-  __shared__ __attribute__((aligned(16))) unsigned char sB3[SB > 3 ? KT * TBYTES : 16];
-  __shared__ __attribute__((aligned(16))) unsigned char sB4[SB > 4 ? KT * TBYTES : 16];
-  __shared__ __attribute__((aligned(16))) unsigned char sB5[SB > 5 ? KT * TBYTES : 16];
   __shared__ int64_t s_dst[BM];
   __shared__ float s_red[XROWS ? 8 : NW][BN];
   __shared__ float s_mean[BN];
@@ -122,10 +119,7 @@ __global__ __launch_bounds__(256 * KV, halo_min_waves(TC, PRO, KV, KP)) void con
     constexpr int b = decltype(bc)::value;
     if constexpr (b == 0) return sB0;
     else if constexpr (b == 1) return sB1;
-    else if constexpr (b == 2) return sB2;
-    else if constexpr (b == 3) return sB3;
-    else if constexpr (b == 4) return sB4;
-    else return sB5;
+    else return sB2;
   };
 
   const TileId T{(int)blockIdx.x, (int)blockIdx.y, 0};
@@ -554,9 +548,6 @@ __global__ __launch_bounds__(256 * KV, halo_min_waves(TC, PRO, KV, KP)) void con
   issue_halo(Ic<0>{}, 0);
   issue_b(Ic<0>{}, 0);
   if constexpr (D >= 2) issue_b(Ic<1>{}, 1);
-  if constexpr (D >= 3) issue_b(Ic<2>{}, 2);
-  if constexpr (D >= 4) issue_b(Ic<3>{}, 3);
-  if constexpr (D >= 5) issue_b(Ic<4>{}, 4);
   // destination offsets of the tile's rows (the epilogue's), under the first loads
   for (int r = tid; r < BM; r += NW * 64) {
     const int m = TC > 0 ? (img2 * H + h0 + r / (TC > 0 ? TC : 1)) * W + w0 + r % (TC > 0 ? TC : 1) : m0 + r;

@@ -5,8 +5,8 @@
 // steps of 64 consecutive pixels, no halo, chunks of up to 288 input channels).
 //
 // A block owns one tile of output channels (64 or 96 rows) by one chunk of input channels
-// (32, or 48 where that pads the channels less) across all nine taps, and walks a contiguous range of PR x PC pixel patches of one image each.  Per
-// patch it stages in LDS, once, the patch's dy pixels and the (PR + 2) x (PC + 2) input
+// (32, or 48 where that pads the channels less) across all nine taps, and walks a contiguous
+// range of PR x PC pixel patches of one image each.  Per patch it stages in LDS, once, the patch's dy pixels and the (PR + 2) x (PC + 2) input
 // pixels that the nine taps reach (zeros outside the image), and reads every tap's MFMA
 // operand out of that halo with transposing LDS reads at the tap's pixel shift.  The
 // general weight-gradient kernel gathers each tap's input rows for every 128-column tile,

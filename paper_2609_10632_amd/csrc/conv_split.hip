@@ -14,29 +14,14 @@
 // Channel counts are any multiple of 8 (a lane's 16-byte chunk never splits a tap): each lane
 // derives the tap and channel of its chunk from the reduction index by an exact division.
 #include <cstdlib>
-#include <type_traits>
 
-#include "kernels.h"
+#include "conv_tile.h"
 
 namespace numbat {
 
 namespace {
 
-constexpr uint32_t kOobS = 0x80000000u;  // an offset past every buffer range: the load returns zeros
-constexpr int kRecS = 0x7ffffff0;
 constexpr int kBK = 64;  // reduction elements per step
-
-typedef __attribute__((address_space(3))) void slds_void_t;
-typedef short sv4s_t __attribute__((ext_vector_type(4)));
-typedef unsigned sv2u_t __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) sv4s_t slds_v4s_t;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t srsrc(const void* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, kRecS, 0x00020000);
-}
-
-template <int V>
-using IcS = std::integral_constant<int, V>;
 
 // TM x TN blocks of 32 x 32 per tile, NW waves, two stages per wave
 template <int TM, int TN, int NW>
@@ -54,12 +39,6 @@ struct SplitShape {
   static_assert(S0 + NW * STG + 8 * BM + 4 * (NG + 1) * BN <= 160 * 1024, "LDS");
   static_assert(NT >= BN, "a thread per column");
 };
-
-// slot swizzle of a transposed weight stage ([64 reduction rows][BN columns])
-template <int BN>
-__device__ __forceinline__ int split_bt_swizzle(int r) {
-  return BN == 64 ? 4 * ((r >> 1) & 1) : 0;
-}
 
 template <int TM, int TN, int NW, bool BT>
 __global__ __launch_bounds__(64 * NW) void convsplit_kernel(ConvGemmArgs a, FastDiv dcs) {
@@ -80,56 +59,26 @@ __global__ __launch_bounds__(64 * NW) void convsplit_kernel(ConvGemmArgs a, Fast
   if (a.remap) lg = xcd_remap(lg, gx * gy * gridDim.z);
   const int mt = (int)(lg % gx), nt = (int)((lg / gx) % gy), phase = (int)(lg / (gx * gy));
   const GemmPhase& P = a.ph[phase];
+  const Geo Ge = load_geo(P);
   const int m0 = mt * BM, n0 = nt * BN;
   if (m0 >= P.m) return;  // this phase has fewer tiles; uniform exit before any barrier
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const int cs = a.cs, ktot = P.ktot, taps = P.taps, nout = a.nout;
-  const int ghw = P.gh * P.gw;
 
   // ---- A: instruction q of a stage fills rows 8 q + lane / 8; the lane's slot lane % 8 holds
   // 16-byte chunk slot ^ ((row / 2) % 8) of the row's 64 reduction elements
   const int lrow = lane >> 3;
   const int kc0 = (lane & 7) ^ (lrow >> 1);  // even q; odd q: kc0 ^ 4
   const uint32_t img0 = fdiv((uint32_t)m0, P.div_ghw);
-  const __amdgpu_buffer_rsrc_t rsA = srsrc(a.src + ((int64_t)img0 * a.hs * a.ws - a.halo_px) * a.src_pix);
-  const __amdgpu_buffer_rsrc_t rsB = srsrc(P.wt);
+  const __amdgpu_buffer_rsrc_t rsA = buffer_rsrc(a.src + ((int64_t)img0 * a.hs * a.ws - a.halo_px) * a.src_pix);
+  const __amdgpu_buffer_rsrc_t rsB = buffer_rsrc(P.wt);
   uint32_t vrow[AI], vmask[AI];
-  const int tw = P.tw, th = P.th;
+  const int tw = P.tw;
 #pragma unroll
-  for (int q = 0; q < AI; ++q) {
-    const int m = m0 + 8 * q + lrow;
-    vrow[q] = 0;
-    vmask[q] = 0;
-    if (m < P.m) {
-      const uint32_t img = fdiv((uint32_t)m, P.div_ghw);
-      const uint32_t rem = (uint32_t)m - img * (uint32_t)ghw;
-      const uint32_t gi = fdiv(rem, P.div_gw);
-      const int ih0 = (int)gi * a.gstride_h, iw0 = (int)(rem - gi * (uint32_t)P.gw) * a.gstride_w;
-      vrow[q] = (uint32_t)((((int64_t)(img - img0) * a.hs + ih0) * a.ws + iw0) * (a.src_pix * 2));
-      uint32_t cols = 0, mk = 0;
-#pragma unroll
-      for (int j = 0; j < 5; ++j)
-        cols |= (j < tw && (unsigned)(iw0 + P.dw0 + j * P.tsw) < (unsigned)a.ws ? 1u : 0u) << j;
-#pragma unroll
-      for (int i = 0; i < 5; ++i)
-        mk |= (i < th && (unsigned)(ih0 + P.dh0 + i * P.tsh) < (unsigned)a.hs ? cols : 0u) << (i * tw);
-      vmask[q] = mk;  // bits >= taps stay clear
-    }
-  }
-  for (int r = tid; r < BM; r += NT) {
-    const int m = m0 + r;
-    int64_t d = -1;
-    if (m < P.m) {
-      const uint32_t img = fdiv((uint32_t)m, P.div_ghw);
-      const uint32_t rem = (uint32_t)m - img * (uint32_t)ghw;
-      const uint32_t gi = fdiv(rem, P.div_gw);
-      d = (((int64_t)img * a.hd + (int)gi * a.dstep_h + P.doff_h) * a.wd + (int)(rem - gi * (uint32_t)P.gw) * a.dstep_w +
-           P.doff_w) * a.dst_pix;
-    }
-    s_dst[r] = d;
-  }
+  for (int q = 0; q < AI; ++q) row_gather(a, Ge, m0 + 8 * q + lrow, img0, vrow[q], vmask[q]);
+  for (int r = tid; r < BM; r += NT) s_dst[r] = dst_offset(a, Ge, m0 + r);
   // a tap's grid row is (tap * tinv) >> 16 (exact for tap < 32), its byte offsets from there
   const uint32_t tinv = (65536u + (uint32_t)tw - 1) / (uint32_t)tw;
   const uint32_t acol = (uint32_t)P.cstep, arow = (uint32_t)(P.rstep + (tw - 1) * P.cstep), a0 = (uint32_t)P.toff0;
@@ -144,13 +93,13 @@ __global__ __launch_bounds__(64 * NW) void convsplit_kernel(ConvGemmArgs a, Fast
   for (int j = 0; j < BI; ++j) {
     if constexpr (!BT) {
       const int o = n0 + 8 * j + lrow;
-      boff[j] = o < nout ? (uint32_t)((int64_t)o * ktot * 2) : kOobS;
+      boff[j] = o < nout ? (uint32_t)((int64_t)o * ktot * 2) : kOob;
     } else {
       const int byte = j * 1024 + lane * 16;
       const int row = byte / (2 * BN), slot = (byte % (2 * BN)) / 16;
-      const int ch = slot ^ split_bt_swizzle<BN>(row);
+      const int ch = slot ^ bt_swizzle<BN>(row);
       brow[j] = row;
-      boff[j] = n0 + ch * 8 < nout ? (uint32_t)((n0 + ch * 8) * 2) : kOobS;
+      boff[j] = n0 + ch * 8 < nout ? (uint32_t)((n0 + ch * 8) * 2) : kOob;
     }
   }
 
@@ -176,22 +125,22 @@ __global__ __launch_bounds__(64 * NW) void convsplit_kernel(ConvGemmArgs a, Fast
 #pragma unroll
     for (int q = 0; q < AI; ++q) {
       const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)vmask[q], tp[q & 1], 1);
-      const uint32_t vo = (t & (vrow[q] + lo[q & 1])) | (~t & kOobS);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (slds_void_t*)(A + q * 1024), 16, vo, 0, 0, 0);
+      const uint32_t vo = (t & (vrow[q] + lo[q & 1])) | (~t & kOob);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void_t*)(A + q * 1024), 16, vo, 0, 0, 0);
     }
 #pragma unroll
     for (int j = 0; j < BI; ++j) {
       uint32_t vb;
       if constexpr (!BT) {
-        vb = (kk[j & 1] < (uint32_t)ktot && boff[j] != kOobS) ? boff[j] + 2u * kk[j & 1] : kOobS;
+        vb = (kk[j & 1] < (uint32_t)ktot && boff[j] != kOob) ? boff[j] + 2u * kk[j & 1] : kOob;
       } else {
         const uint32_t k = (uint32_t)(kb + brow[j]);
         const uint32_t t = fdiv(k, dcs);
         const uint32_t r = (t * tinv) >> 16;
         const uint32_t wo = w0 + r * wrow + (t - r * (uint32_t)tw) * wcol + (k - t * (uint32_t)cs) * wostep;
-        vb = (t < (uint32_t)taps && boff[j] != kOobS) ? boff[j] + wo : kOobS;
+        vb = (t < (uint32_t)taps && boff[j] != kOob) ? boff[j] + wo : kOob;
       }
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (slds_void_t*)(B + j * 1024), 16, vb, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_void_t*)(B + j * 1024), 16, vb, 0, 0, 0);
     }
   };
 
@@ -213,7 +162,7 @@ __global__ __launch_bounds__(64 * NW) void convsplit_kernel(ConvGemmArgs a, Fast
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int c = 4 * j + 2 * (g & 1) + (q >> 1);
-      btoff[j] = (uint32_t)(r0 * 2 * BN + (c ^ split_bt_swizzle<BN>(r0)) * 16 + (q & 1) * 8);
+      btoff[j] = (uint32_t)(r0 * 2 * BN + (c ^ bt_swizzle<BN>(r0)) * 16 + (q & 1) * 8);
     }
   }
   // this wave's loads of the step are done (the next step's stay in flight); read its
@@ -234,9 +183,9 @@ __global__ __launch_bounds__(64 * NW) void convsplit_kernel(ConvGemmArgs a, Fast
           bf[ks][j] = *reinterpret_cast<const u32x4*>(B + j * 32 * 128 + ko);
         } else {
           const unsigned char* pb = B + btoff[j] + ks * 16 * 2 * BN;
-          const sv4s_t r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((slds_v4s_t*)pb);
-          const sv4s_t r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((slds_v4s_t*)(pb + 4 * 2 * BN));
-          const sv2u_t lo = __builtin_bit_cast(sv2u_t, r0), hi = __builtin_bit_cast(sv2u_t, r1);
+          const v4s_t r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_t*)pb);
+          const v4s_t r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_t*)(pb + 4 * 2 * BN));
+          const v2u_t lo = __builtin_bit_cast(v2u_t, r0), hi = __builtin_bit_cast(v2u_t, r1);
           bf[ks][j] = u32x4{lo.x, lo.y, hi.x, hi.y};
         }
       }
@@ -252,11 +201,11 @@ __global__ __launch_bounds__(64 * NW) void convsplit_kernel(ConvGemmArgs a, Fast
         for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(af[ks][i], bf[ks][j], acc[i][j]);
   };
   const int nk = (ktot + kBK - 1) / kBK;
-  issue(IcS<0>{}, wave);
-  issue(IcS<1>{}, wave + NW);
+  issue(Ic<0>{}, wave);
+  issue(Ic<1>{}, wave + NW);
   for (int kt = wave; kt < nk; kt += 2 * NW) {
-    step(IcS<0>{}, kt);
-    if (kt + NW < nk) step(IcS<1>{}, kt + NW);
+    step(Ic<0>{}, kt);
+    if (kt + NW < nk) step(Ic<1>{}, kt + NW);
   }
   // the loads issued past the last step land before the stages become the waves' sums
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

@@ -925,12 +925,13 @@ bool convgemm_taps(ConvGemmArgs& a, int bm) {
 
 // Eight-wave tiles whose waves stand in four rows of two: a wave's share of a 256 x 192 tile is
 // 64 x 96 (5 LDS fragments per 6 products), and a CU loads 448 rows per 49152 products where 128
-// x 64 tiles load 192 per 8192: the loads into LDS, which bound the other tiles, fall behind
-// the products.  One block per CU, so the grid has to fill whole rounds of 256 blocks: the
-// tile is taken where the GEMM's own area is at least a share `eff` of the rounds' area and
-// nout fills its columns to 10%.  Measured, us, against the rule below it:
-//  forward (eff 0.6, reductions of 256 or more, past two rounds of 512): 16 x 40 x 40, 960 -> 384 (0.78) 33.7 -> 29.0, 80 x
-//   80, 576 -> 192 (0.78) 63.4 -> 48.2, 160 x 160 stride 2, 96 -> 192 (0.78) 64.5 -> 55.9; 12 x 52 x 52 x
+// x 64 tiles load 192 per 8192.  Latency still bounds it (the matrix cores are busy a quarter of
+// the time: 35% of the waves' cycles wait for loads, 34% at the barrier or to issue), but less: 160 x
+// 160 stride 2, 96 -> 192 19 -> 25% busy.  One block per CU, so the grid has to fill whole rounds
+// of 256 blocks: the tile is taken where the GEMM's own area is at least a share `eff` of the
+// rounds' area and nout fills its columns to 10%.  Measured, us, against the rule below it:
+//  forward (eff 0.6, reductions of 256 or more, past two rounds of 512): 16 x 40 x 40, 960 -> 384
+//   (0.78) 33.7 -> 29.0, 80 x 80, 576 -> 192 (0.78) 63.4 -> 48.2, 160 x 160 stride 2, 96 -> 192 (0.78) 64.5 -> 55.9; 12 x 52 x 52 x
 //   256 on 256 x 128 (0.99) 17.8 -> 12.1, 100 x 100 stride 2, 64 -> 128 (0.61) 19.6 -> 14.0; 40 x 40 x 320
 //   (0.65, a sixth of the columns idle) 15.1 -> 16.4.  Short reductions are bound by memory, and
 //   one block per CU overlaps its output with nothing: training passes of 80 x 80 x 192 148.8

@@ -76,8 +76,8 @@ constexpr int halo_min_waves(int tc, int pro, int kv, int kp) {
 // PRO (kProFwd, kProBwd): an element-wise prologue on each 32-channel chunk of the staged
 // halo, once per element, before any tap reads it; its per-channel constants sit in dynamic
 // LDS (2 or 4 floats per source channel, sized at launch), and the loading lanes (of a
-// forward's two halves, both on linear tiles) transform their chunks between their load wait and the barrier.  kProBwd (the data gradient,
-// four waves): the halo holds g, each lane also loads y for its own halo chunks (into
+// forward's two halves, both on linear tiles) transform their chunks between their load wait
+// and the barrier.  kProBwd (the data gradient, four waves): the halo holds g, each lane also loads y for its own halo chunks (into
 // registers, a chunk ahead), and dy = BN + SiLU backward (g, y) replaces g in place; dy of
 // the tile's own pixels is also stored (first column tile only).
 template <int TM, int TN, int HI, int KT, int SB, bool BT, int TC, int PRO, int KV, int KP, bool TL>
@@ -735,9 +735,9 @@ static bool linear256_fills(int64_t tiles256, int cs) {
 }
 // 96 or 64 columns per tile (3 or 2): 96 for their multiples (of a forward from 256 tiles up: 9 x 23 x
 // 23, 176 -> 192 16.8 us, 14.0 on 64 columns); other counts take the one with less work per CU (its
-// most tiles times their columns) unless eight-wave tiles of 96 fill their rounds.  Data gradients, us, 64 against 96 columns: 14 x 14, 136 <- 64 6.7 : 8.4, 22 x 29 x 29, 152 <-
-// 80 11.4 : 13.5, 4 x 53 x 53, 560 <- 64 15.7 : 18.0; forward 14 x 28 x 28, 128 -> 272 17.5 : 20.2; 16 x 80 x
-// 80, 192 -> 80 52.0 : 39.9.
+// most tiles times their columns) unless eight-wave tiles of 96 fill their rounds.  Data gradients,
+// us, 64 against 96 columns: 14 x 14, 136 <- 64 6.7 : 8.4, 22 x 29 x 29, 152 <- 80 11.4 : 13.5, 4 x 53 x 53,
+// 560 <- 64 15.7 : 18.0; forward 14 x 28 x 28, 128 -> 272 17.5 : 20.2; 16 x 80 x 80, 192 -> 80 52.0 : 39.9.
 static int halo_columns(int64_t m, int nout, int cs, int w, bool bt) {
   const int64_t c96 = (nout + 95) / 96, c64 = (nout + 63) / 64;
   if (c96 * 96 > c64 * 64) return 2;
